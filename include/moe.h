@@ -80,18 +80,16 @@ typedef enum {
      k = 8w+j sits in bits [4j,4j+4) of word w (low nibble first):
      w[e][n][K/8] (int32_t); bf16 scale per 128 along K: scale[e][n][k/128];
      value = q * scale.  Hidden rows enter as bf16 and the SwiGLU
-     intermediate is rounded to bf16.  The first product sums each 128-group
-     of codes exactly and applies the group's scale in fp32; the second
-     rounds q * scale to bf16 before its products, except at decode sizes
-     (T * top_k <= 8 * E, H and I in {512, 1024, 1536, 2048, 3072, 4096}),
-     where both products take the first one's exact form.  A scale may be zero;
-     the nonzero scales must be normal numbers within a factor 2^64 of each
-     other along a weight row (other scales are unspecified): above the
-     decode sizes the first product carries its running sums divided by the
-     current group's scale, so a ratio r between groups multiplies them by r,
-     and 2^64 keeps them inside the fp32 range with about 2^30 to spare for
-     the sums themselves (the decode sizes scale each group's own partial
-     and have no such limit).
+     intermediate is rounded to bf16.  Both products sum each 128-group of
+     codes exactly (as 136 + q, less 136 times the group's activations) and
+     apply the group's scale in fp32.  A scale may be zero; the nonzero scales
+     must be normal numbers within a factor 2^64 of each other along a weight
+     row (other scales are unspecified): above the decode sizes (T * top_k <=
+     8 * E, H and I in {512, 1024, 1536, 2048, 3072, 4096}) the products carry
+     their running sums divided by the current group's scale, so a ratio r
+     between groups multiplies them by r, and 2^64 keeps them inside the fp32
+     range with about 2^30 to spare for the sums themselves (the decode sizes
+     scale each group's own partial and have no such limit).
      Scales from a per-group amax quantiser of real weight rows differ by a
      few powers of two. */
   MOE_W_INT4_G128 = 2,
@@ -259,7 +257,10 @@ typedef struct moe_ws_layout {
                                         of the hidden rows (times -136), not
                                         written at the decode sizes above     */
   int64_t inter, inter_s;            /* bf16 [cap,I] (fp8: uint8 [cap,I], fp32 [cap,I/128];
-                                        MXFP8: uint8 [cap,I], uint8 [cap,I/32] E8M0) */
+                                        MXFP8: uint8 [cap,I], uint8 [cap,I/32] E8M0;
+                                        int4 above the decode sizes: every eight
+                                        columns in the order {0,4,1,5,2,6,3,7},
+                                        their group sums at the workspace's end) */
   int64_t y;                         /* [cap,H] rows in sorted order: bf16 for
                                         MOE_W_FP8E4M3_B128 and MOE_W_MXFP4_MXFP8,
                                         fp32 otherwise; pad rows unspecified */

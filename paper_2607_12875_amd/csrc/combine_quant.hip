@@ -212,12 +212,15 @@ hipError_t launch_act_quant_mx(const uint16_t* x, int M, int K, uint8_t* q, uint
 }
 
 // Per (row, 128-column group): -136 times the fp32 sum of the group's values,
-// the term the int4 GEMM1 takes off its biased codes (136 + q).  Sixteen
-// lanes (one DPP row) own one group, as in the quantiser above.
+// the term the int4 products take off their biased codes (136 + q).  Sixteen
+// lanes (one DPP row) own one group, as in the quantiser above.  With xp the
+// eight columns of each thread also go out in the order the codes decode to
+// (dword d: columns d and d + 4).  With rows, only that many rows are live.
 __global__ __launch_bounds__(256) void group_sum_kernel(const uint16_t* __restrict__ x, int M, int K,
-                                                         float* __restrict__ out) {
+                                                         float* __restrict__ out, uint16_t* __restrict__ xp,
+                                                         const int32_t* __restrict__ rows) {
   const long idx = static_cast<long>(blockIdx.x) * 256 + threadIdx.x;  // one per 8 columns
-  const long total = static_cast<long>(M) * (K / 8);
+  const long total = static_cast<long>(rows ? min(*rows, M) : M) * (K / 8);
   const bool live = idx < total;
   uint4 v = make_uint4(0, 0, 0, 0);
   if (live) v = *reinterpret_cast<const uint4*>(x + idx * 8);
@@ -229,13 +232,19 @@ __global__ __launch_bounds__(256) void group_sum_kernel(const uint16_t* __restri
   sum += dpp_f32<0x4E>(sum);
   sum += dpp_f32<0x141>(sum);
   sum += dpp_f32<0x140>(sum);
-  if (live && (threadIdx.x & 15) == 0) out[idx / 16] = -136.0f * sum;
+  if (!live) return;
+  if ((threadIdx.x & 15) == 0) out[idx / 16] = -136.0f * sum;
+  if (xp)
+    *reinterpret_cast<uint4*>(xp + idx * 8) =
+        make_uint4(__builtin_amdgcn_perm(v.z, v.x, 0x05040100u), __builtin_amdgcn_perm(v.z, v.x, 0x07060302u),
+                   __builtin_amdgcn_perm(v.w, v.y, 0x05040100u), __builtin_amdgcn_perm(v.w, v.y, 0x07060302u));
 }
 
-hipError_t launch_group_sum(const uint16_t* x, int M, int K, float* out, hipStream_t st) {
+hipError_t launch_group_sum(const uint16_t* x, int M, int K, float* out, uint16_t* xp, const int32_t* rows,
+                            hipStream_t st) {
   const long total = static_cast<long>(M) * (K / 8);
   const dim3 grid(static_cast<unsigned>((total + 255) / 256)), block(256);
-  hipLaunchKernelGGL(group_sum_kernel, grid, block, 0, st, x, M, K, out);
+  hipLaunchKernelGGL(group_sum_kernel, grid, block, 0, st, x, M, K, out, xp, rows);
   return hipGetLastError();
 }
 

@@ -12,13 +12,19 @@
 //        the next blocks' MFMAs.  The GEMM1 epilogue requantises the
 //        intermediate per (row, 128 columns): the tile holds exactly one such
 //        group per row.
-//  int4  A bf16; B signed int4 words decoded in registers (q * bf16 scale,
-//        rounded to bf16) right before the bf16 MFMA, never materialised.
+//  int4  A bf16; B signed int4 words decoded in registers to the exact bf16
+//        136 + q right before the bf16 MFMA, never materialised; the bias comes
+//        off through the activations' group sums and the group scale is applied
+//        to the fp32 sums.  VALU-bound by the decode at two workgroups per CU:
+//        with 7 operations per word (14 in the first product and 28, a rounded
+//        q * scale per code, in the second before) a layer of 512 tokens,
+//        4096 x 1536 x 128 experts, top 8, takes 388 us (433).
 //  mxfp4 A bf16; B OCP MX E2M1 codes with an E8M0 scale per 32 elements,
 //        decoded by v_cvt_scalef32_pk_bf16_fp4 (exact: the bf16 result is the
 //        code's value times a power of two) right before the bf16 MFMA.
-// Every GEMM2 also forms its product transposed (four consecutive output
-// columns per lane, so y goes out in 16-byte stores).
+// Every GEMM2 but int4's (whose scales and biases fit the direct layout) also
+// forms its product transposed (four consecutive output columns per lane, so y
+// goes out in 16-byte stores).
 //
 // Each K step streams KB bytes of every A row through LDS -- 128 (64 bf16 /
 // 128 fp8 elements), or 256 for the 4-bit formats (128 elements, so each
@@ -48,31 +54,18 @@ constexpr int MOE_MAX_EXPERTS_DEV = 1024;  // the ABI's expert limit
 // last step multiplies zeros and reads nothing beyond a row.
 __device__ __align__(16) const uint8_t kZeroChunk[16] = {};
 
-// 8 signed nibbles -> 8 bf16 values q * s (s an fp32 copy of a bf16 scale).
-__device__ __forceinline__ bf16x8 dequant_int4x8(uint32_t w, float s) {
-  bf16x8 r;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int q = static_cast<int>(w << (28 - 4 * i)) >> 28;
-    r[i] = static_cast<__bf16>(static_cast<float>(q) * s);
-  }
-  return r;
-}
-
 // 8 signed nibbles -> 8 bf16 values 136 + q, exact: the bits are 0x4300 | (q + 8)
-// (128 + (q + 8), the nibble in the low mantissa bits of 128).  Element k of
-// the word (bits [4k, 4k+4)) lands in half k % 2 of dword k / 2.  `keep` = 0
-// turns every code into q = 0.  The v_bitop3 immediate is the truth table
-// over (S0, S1, S2) = (0xF0, 0xCC, 0xAA): 0x6A = (S0 & S1) ^ S2.
-__device__ __forceinline__ bf16x8 int4x8_biased_bf16(uint32_t w, uint32_t keep) {
-  const uint32_t y = __builtin_amdgcn_bitop3_b32(w, keep, 0x88888888u, 0x6A);  // q + 8 per nibble
-  const uint32_t y4 = y >> 4;                                                  // odd nibbles moved down
-  u32x4 r;
-  r.x = (__builtin_amdgcn_perm(y4, y, 0x0c040c00u) & 0x000F000Fu) | 0x43004300u;
-  r.y = (__builtin_amdgcn_perm(y4, y, 0x0c050c01u) & 0x000F000Fu) | 0x43004300u;
-  r.z = (__builtin_amdgcn_perm(y4, y, 0x0c060c02u) & 0x000F000Fu) | 0x43004300u;
-  r.w = (__builtin_amdgcn_perm(y4, y, 0x0c070c03u) & 0x000F000Fu) | 0x43004300u;
-  return as_bf16x8(r);
+// (128 + (q + 8), the nibble in the low mantissa bits of 128), and q + 8 = n ^ 8.
+// Dword d takes nibbles d and d + 4, so slot s of the result holds element
+// {0,4,1,5,2,6,3,7}[s] of the word and each dword is one v_bitop3 on the word
+// shifted right by 4 d (truth table of (S0 & S1) ^ S2 over (0xF0, 0xCC, 0xAA):
+// 0x6A): 7 operations per word, where the word's own order took 14.  The
+// activations are stored in the same order (hidden by group_sum_kernel, the
+// intermediate by GEMM1's epilogue).  `mask` is 0x000F000F, or 0 to turn every
+// code into q = 0.
+__device__ __forceinline__ bf16x8 int4x8_biased_bf16(uint32_t w, uint32_t mask) {
+  auto dw = [&](uint32_t v) { return static_cast<uint32_t>(__builtin_amdgcn_bitop3_b32(v, mask, 0x43084308u, 0x6A)); };
+  return as_bf16x8(u32x4{dw(w), dw(w >> 4), dw(w >> 8), dw(w >> 12)});
 }
 
 // XOR swizzle of the 16-byte chunks of a 128-byte LDS row: row r stores its
@@ -112,9 +105,9 @@ void moe_gemm_tiled(GroupedGemm g) {
   constexpr int KE = A8 ? KB : KB / 2;                                 // K elements per step
   constexpr int BB = B4 ? KE / 2 : KB;                                 // B bytes per row per step
   constexpr int LPB = BB / 16;                                         // lanes per 4-bit B row in a copy
-  // bf16 and int4 GEMM2 form their product transposed, as fp8 does (16-byte
+  // bf16 and MXFP4 GEMM2 form their product transposed, as fp8 does (16-byte
   // y stores, one pad check per row; bf16 prefill 4 % faster, GEMM1 was not)
-  constexpr bool TRB = !A8 && !GEMM1;
+  constexpr bool TRB = !A8 && !GEMM1 && FMT != 2;
   constexpr int RPI = 1024 / KB, LPR = KB / 16;  // rows per DMA instruction, lanes per row
   constexpr int WTM = BM / WM, WTN = BNW / WN;
   constexpr int TM = WTM / 32, TN = WTN / 32;
@@ -128,13 +121,13 @@ void moe_gemm_tiled(GroupedGemm g) {
   // per-stage scale block: NW slots of 256 bytes, one 4-byte DMA instruction
   // each (64 floats); fp8: slots [0, BM/64) the row scales of A, slot BM/64
   // the block scales of B; int4: slots [0, BNW/64) the bf16 pair holding each
-  // B row's group scale, int4 GEMM1 also slots [BNW/64, BNW/64 + BM/64) the
+  // B row's group scale and slots [BNW/64, BNW/64 + BM/64) the
   // rows' biased group sums (x_gsum).  Copy wave lw fills slots lw, lw + LW, ...
   // MXFP8: MXD E8M0 dwords per row per step (four 32-element blocks each);
   // slots [0, MXD BM/64) the A rows' dwords (slot d BM/64 + g: dword d of
   // row group g), then MXD BNW/64 slots of the B rows' likewise; slots past
   // those load a harmless dummy.
-  constexpr bool GSUM = FMT == 2 && GEMM1;
+  constexpr bool GSUM = FMT == 2;
   constexpr int MXD = MX8 ? KE / 128 : 1;
   constexpr int NSLOT = FMT == 0 ? 0 : (MX8 ? MXD * (BM + BNW) / 64 : (GSUM ? 2 : 1) * NW);
   constexpr int SC = (NSLOT + LW - 1) / LW;  // scale loads per copy wave per stage
@@ -307,8 +300,9 @@ void moe_gemm_tiled(GroupedGemm g) {
                                                       (static_cast<size_t>(e) * (GEMM1 ? 2 * g.I : g.H) + n) * (K / 128));
           src.ss[k] = 1;  // advanced per step in elements below
         } else if (GSUM && sl < BNW / 64 + BM / 64) {
-          // row (sl - BNW/64)*64 + lane: its token's sum over K step kt's group, one float per step
-          src.s[k] = reinterpret_cast<const uint8_t*>(g.x_gsum + token(sid[A_CH + k]) * (g.H / 128));
+          // row (sl - BNW/64)*64 + lane: its sum over K step kt's group, one float per step
+          if (GEMM1) src.s[k] = reinterpret_cast<const uint8_t*>(g.x_gsum + token(sid[A_CH + k]) * (g.H / 128));
+          else src.s[k] = reinterpret_cast<const uint8_t*>(g.inter_gsum + static_cast<size_t>(m0 + (sl - BNW / 64) * 64 + lane) * (g.I / 128));
           src.ss[k] = 4;
         }
       } else if constexpr (MX8) {
@@ -372,7 +366,7 @@ void moe_gemm_tiled(GroupedGemm g) {
     if (q1 < N_DMA) return;
 #pragma unroll
     for (int k = 0; k < SC; ++k) {
-      // int4 GEMM1 (two stages, so every wait drains all loads and the
+      // int4 (two stages, so every wait drains all loads and the
       // per-wave load counts need not match) skips its empty slots
       if (GSUM && src.ss[k] == 0) continue;
       const uint32_t dst = base + A_BYTES + B_BYTES + (lw + k * LW) * 256;
@@ -486,7 +480,10 @@ void moe_gemm_tiled(GroupedGemm g) {
     // check, requested before the K loop (the math waves issue no other
     // global loads, so this one has landed long before it is used)
     int sid_ep[GEMM1 ? 1 : TM];
-    if constexpr (!GEMM1) {
+    bool live_row = false;  // int4: row m0 + lane of the tile
+    if constexpr (!GEMM1 && FMT == 2) {
+      live_row = g.sorted_ids[m0 + lane] < g.n_routed;
+    } else if constexpr (!GEMM1) {
 #pragma unroll
       for (int i = 0; i < TM; ++i) sid_ep[i] = g.sorted_ids[m0 + wm * WTM + i * 32 + l32];
     }
@@ -495,7 +492,7 @@ void moe_gemm_tiled(GroupedGemm g) {
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j) acc[i][j] = f32x16{};
-    float seff[TN];  // int4 GEMM1: the scale each column's accumulators are divided by (0: none yet)
+    float seff[TN];  // int4: the scale each column's accumulators are divided by (0: none yet)
 #pragma unroll
     for (int j = 0; j < TN; ++j) seff[j] = 0.f;
 
@@ -730,7 +727,7 @@ void moe_gemm_tiled(GroupedGemm g) {
           __builtin_amdgcn_sched_barrier(0);
         }
       } else if constexpr (GSUM) {
-        // int4 GEMM1.  The codes enter the MFMA exactly, as bf16 136 + q, and
+        // int4.  The codes enter the MFMA exactly, as bf16 136 + q, and
         // the group scale is applied in fp32: acc holds the tile's sum
         // divided by its column's current scale s, so each step first takes
         // acc * (s_prev / s) - 136 * (the row's sum over the group) and the
@@ -744,17 +741,17 @@ void moe_gemm_tiled(GroupedGemm g) {
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
           const int r = brow(j) + l32;
-          const int n_glob = r < NC ? n0 + r : g.I + n0 + (r - NC);
+          const int n_glob = GEMM1 ? (r < NC ? n0 + r : g.I + n0 + (r - NC)) : n0 + r;
           // element index of the scale; only its parity (which half of the dword) is
           // used, so unsigned wrap-around for the largest weight tensors is harmless
-          const unsigned idx = (static_cast<unsigned>(e) * 2u * g.I + n_glob) * (K / 128) + (kt * KE) / 128;
+          const unsigned idx = (static_cast<unsigned>(e) * (GEMM1 ? 2u * g.I : g.H) + n_glob) * (K / 128) + (kt * KE) / 128;
           const uint32_t d = sW[r];
           const float sc = __uint_as_float((idx & 1) ? (d & 0xFFFF0000u) : (d << 16));
           const bool z = sc == 0.f;
           const float se = z ? seff[j] : sc;
           ratio[j] = seff[j] == 0.f ? 0.f : seff[j] * __builtin_amdgcn_rcpf(se);  // 1-ulp reciprocal
           seff[j] = se;
-          keep[j] = z ? 0u : ~0u;
+          keep[j] = z ? 0u : 0x000F000Fu;
         }
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
@@ -771,76 +768,39 @@ void moe_gemm_tiled(GroupedGemm g) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = fmaf(acc[i][j][v], ratio[j], rs[v]);
         }
+        // substep kk of lane group kg covers K elements [(NKK*kg+kk)*8, +8) of
+        // the step, chunk NKK*kg + kk of an activation row and word kk % 4 of
+        // chunk NBW*kg + kk/4 of a weight row.  Chunk addresses are one XOR on
+        // the stage's (rows aligned to their bytes), and the scheduler keeps to
+        // one substep at a time: both hold the kernel in 128 registers.
+        static_assert(STAGE % 256 == 0 && A_BYTES % 256 == 0, "rows aligned to their size");
+        const int ra = wm * WTM + l32, rb = brow(0) + l32;
+        const uint32_t st = smem0 + ((sb + kt) % STAGES) * STAGE;
+        const uint32_t pa = st + ra * KB + (((NKK * kg) ^ swz<KB>(ra)) << 4);
+        const uint32_t pb = st + A_BYTES + rb * BB + (((NBW * kg) ^ swz_b<BB>(rb)) << 4);
+        u32x4 bw[TN];
+        bf16x8 a[2][TM];
 #pragma unroll
-        for (int h = 0; h < NBW; ++h) {
-          u32x4 bw[TN];
+        for (int i = 0; i < TM; ++i) a[0][i] = as_bf16x8(lds16(pa + i * 32 * KB));
 #pragma unroll
-          for (int j = 0; j < TN; ++j) {
-            const int r = brow(j) + l32;
-            bw[j] = ld16(Bs + r * BB + (((NBW * kg + h) ^ swz_b<BB>(r)) << 4));
+        for (int kk = 0; kk < NKK; ++kk) {
+          if (kk % 4 == 0) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j) bw[j] = lds16((pb ^ (kk / 4) << 4) + (brow(j) - brow(0)) * BB);
           }
+          if (kk + 1 < NKK) {
 #pragma unroll
-          for (int k4 = 0; k4 < 4; ++k4) {
-            // substep kk of lane group kg covers K elements [(NKK*kg+kk)*8, +8) of the step
-            const int kk = 4 * h + k4, ch = NKK * kg + kk;
-            bf16x8 a[TM], b[TN];
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-              const int r = wm * WTM + i * 32 + l32;
-              a[i] = as_bf16x8(ld16(As + r * KB + ((ch ^ swz<KB>(r)) << 4)));
-            }
-#pragma unroll
-            for (int j = 0; j < TN; ++j) b[j] = int4x8_biased_bf16(bw[j][k4], keep[j]);
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-              for (int j = 0; j < TN; ++j) acc[i][j] = mfma32x32x16(a[i], b[j], acc[i][j]);
+            for (int i = 0; i < TM; ++i) a[(kk + 1) & 1][i] = as_bf16x8(lds16((pa ^ (kk + 1) << 4) + i * 32 * KB));
           }
-        }
-      } else if constexpr (FMT == 2) {
-        // int4 GEMM2: each code is decoded to bf16 q * s before the MFMA;
-        // this lane's scales, then per 64-element half of the step its B words
-        // (one word of eight nibbles per 16-wide K substep; a lane group
-        // covers KE/2 elements of the step)
-        constexpr int NKK = KE / 16, NBW = NKK / 4;
-        const uint32_t* sW = reinterpret_cast<const uint32_t*>(Ss);  // one dword per tile row
-        float sb[TN];
+          __builtin_amdgcn_sched_barrier(0);
+          bf16x8 b[TN];
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const int r = brow(j) + l32;
-          const int n_glob = GEMM1 ? (r < NC ? n0 + r : g.I + n0 + (r - NC)) : n0 + r;
-          const unsigned idx = (static_cast<unsigned>(e) * (GEMM1 ? 2 * g.I : g.H) + n_glob) * (K / 128) + (kt * KE) / 128;
-          const uint32_t d = sW[r];
-          sb[j] = __uint_as_float((idx & 1) ? (d & 0xFFFF0000u) : (d << 16));
-        }
+          for (int j = 0; j < TN; ++j) b[j] = int4x8_biased_bf16(bw[j][kk % 4], keep[j]);
 #pragma unroll
-        for (int h = 0; h < NBW; ++h) {
-          u32x4 bw[TN];
+          for (int i = 0; i < TM; ++i)
 #pragma unroll
-          for (int j = 0; j < TN; ++j) {
-            const int r = brow(j) + l32;
-            bw[j] = ld16(Bs + r * BB + (((NBW * kg + h) ^ swz_b<BB>(r)) << 4));
-          }
-#pragma unroll
-          for (int k4 = 0; k4 < 4; ++k4) {
-            // substep kk of lane group kg covers K elements [(NKK*kg+kk)*8, +8) of the step
-            const int kk = 4 * h + k4, ch = NKK * kg + kk;
-            bf16x8 a[TM], b[TN];
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-              const int r = wm * WTM + i * 32 + l32;
-              a[i] = as_bf16x8(ld16(As + r * KB + ((ch ^ swz<KB>(r)) << 4)));
-            }
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-              const uint32_t wd = k4 == 0 ? bw[j].x : (k4 == 1 ? bw[j].y : (k4 == 2 ? bw[j].z : bw[j].w));
-              b[j] = dequant_int4x8(wd, sb[j]);
-            }
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-              for (int j = 0; j < TN; ++j) acc[i][j] = TRB ? mfma32x32x16(b[j], a[i], acc[i][j]) : mfma32x32x16(a[i], b[j], acc[i][j]);
-          }
+            for (int j = 0; j < TN; ++j) acc[i][j] = mfma32x32x16(a[kk & 1][i], b[j], acc[i][j]);
+          __builtin_amdgcn_sched_barrier(0);
         }
       } else if constexpr (MX8) {
         // MXFP4 weights x MXFP8 activations, formed transposed like fp8 (the
@@ -944,16 +904,16 @@ void moe_gemm_tiled(GroupedGemm g) {
     // transposed (W is the MFMA's first operand): lane (kg, l32) of row
     // block i holds row wm*WTM + i*32 + l32 at columns 8*(v/4) + 4*kg + v%4
     // of each column block, so four consecutive columns per store.
+    if constexpr (GSUM) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[i][j][v] *= seff[j];
+    }
     if constexpr (GEMM1) {
       constexpr int TH = TN / 2;  // gate tiles (paired with up tile j + TH)
-      if constexpr (GSUM) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] *= seff[j];
-      }
       float av[TM][TH][16];
 #pragma unroll
       for (int i = 0; i < TM; ++i)
@@ -1046,7 +1006,9 @@ void moe_gemm_tiled(GroupedGemm g) {
 #pragma unroll
               for (int v = 0; v < 16; ++v) {
                 const int row = m0 + wm * WTM + i * 32 + 8 * (v >> 2) + 4 * kg + (v & 3);
-                const int col = n0 + wn * (WTN / 2) + j * 32 + l32;
+                // int4: eight columns in the order the second product's codes decode to
+                const int lc = FMT == 2 ? (l32 & ~7) | (l32 & 3) << 1 | (l32 >> 2 & 1) : l32;
+                const int col = n0 + wn * (WTN / 2) + j * 32 + lc;
                 if (!masked || col < g.I) o[static_cast<size_t>(row) * g.I + col] = f32_to_bf16(av[i][j][v]);
               }
         };
@@ -1082,9 +1044,23 @@ void moe_gemm_tiled(GroupedGemm g) {
             *reinterpret_cast<u32x4*>(yr + col) = o;
           }
       }
+    } else if constexpr (FMT == 2) {
+      // direct layout, fp32 y: the tile's routed rows come before its pads
+      const int live = __popcll(__ballot(live_row)) - 4 * kg;
+      static_assert(FMT != 2 || BM == 64, "one row per lane in the ballot");
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int r = wm * WTM + i * 32 + 8 * (v >> 2) + (v & 3);
+          if (r >= live) continue;  // pad rows are never read
+          float* yr = static_cast<float*>(g.y) + static_cast<size_t>(m0 + r + 4 * kg) * g.H + n0 + wn * WTN + l32;
+#pragma unroll
+          for (int j = 0; j < TN; ++j) yr[j * 32] = acc[i][j][v];
+        }
     } else {
       // transposed layout, fp32 y: four consecutive output columns per 16-byte store
-      static_assert(TRB && y_is_f32(FMT), "bf16 and int4 routes keep y in fp32");
+      static_assert(TRB && y_is_f32(FMT), "bf16-activation routes keep y in fp32");
       const bool masked = n0 + NC > g.H;  // uniform: only a ragged last column tile masks
 #pragma unroll
       for (int i = 0; i < TM; ++i) {

@@ -32,15 +32,19 @@ hipError_t launch_combine(const void* y, bool y_f32, const float* w, const int32
 hipError_t launch_act_quant(const uint16_t* x, int M, int K, uint8_t* q, float* s, hipStream_t st);
 // OCP MX e4m3 per (row, 32 columns): codes q [M,K] and E8M0 bytes sx [M,K/32]
 hipError_t launch_act_quant_mx(const uint16_t* x, int M, int K, uint8_t* q, uint8_t* sx, hipStream_t st);
-// out[m][g] = -136 * sum of x[m][128g, 128g + 128) in fp32 (int4 GEMM1's bias term)
-hipError_t launch_group_sum(const uint16_t* x, int M, int K, float* out, hipStream_t st);
+// out[m][g] = -136 * sum of x[m][128g, 128g + 128) in fp32 (the int4 products'
+// bias term).  xp, if given, receives x with every eight columns in the order
+// {0,4,1,5,2,6,3,7} (the order the int4 codes decode to); rows, if given, is
+// the device count of rows to do (at most M).
+hipError_t launch_group_sum(const uint16_t* x, int M, int K, float* out, uint16_t* xp, const int32_t* rows,
+                            hipStream_t st);
 
 // Grouped expert GEMMs.  Rows are the permuted routed rows (sorted order),
 // grouped by expert in segments padded to a multiple of the kernel's row tile;
 // `offsets` is the permute's expert_offsets[E+1], `max_rows` the capacity.
 struct GroupedGemm {
   // first product: A rows are hidden[sorted_ids[p] / top_k] (pads read row 0)
-  const void* x;              // bf16 hidden [T,H] (fp8, MXFP8: e4m3 codes [T,H])
+  const void* x;              // bf16 hidden [T,H] (fp8, MXFP8: e4m3 codes [T,H]; tiled int4: column order of launch_group_sum)
   const float* x_scale;       // fp8 only: [T, H/128]
   const uint8_t* x_mx;        // MXFP8 only: E8M0 bytes [T, H/32]
   const float* x_gsum;        // int4 only: [T, H/128], -136 * the sum of each 128-group of a hidden row
@@ -53,6 +57,7 @@ struct GroupedGemm {
   const void* w2_scale;
   void* inter;                // [cap, I] bf16 (fp8, MXFP8: e4m3 codes)
   float* inter_scale;         // fp8 only: [cap, I/128]
+  const float* inter_gsum;    // tiled int4 only: [cap, I/128], -136 * the sum of each 128-group of an intermediate row
   uint8_t* inter_mx;          // MXFP8 only: E8M0 bytes [cap, I/32]
   void* y;                    // [cap, H]: fp32 for bf16 weights, bf16 otherwise
 };

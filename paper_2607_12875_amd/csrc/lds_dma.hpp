@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "common.hpp"
+
 namespace moe {
 
 // One 16-byte (or 4-byte) element per lane: lane l lands at LDS byte
@@ -29,6 +31,11 @@ __device__ __forceinline__ void dma4(const void* gptr, uint32_t lds) {
 }
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(p)));
+}
+// 16 bytes at LDS byte `a` (as lds_addr gives it).
+__device__ __forceinline__ u32x4 lds16(uint32_t a) {
+  const u32x4 v = *(const __attribute__((address_space(3))) u32x4*)a;
+  return v;
 }
 // s_waitcnt with only the vector-memory count: at most N loads outstanding.
 // The signal fences keep the compiler from moving LDS reads of the data the

@@ -69,6 +69,13 @@ moe_status check_args(const moe_args* a) {
   return MOE_OK;
 }
 
+// Tiled int4: the intermediate rows' group sums (one fp32 per 128 columns, 1/64
+// of the intermediate's own bytes).
+size_t int4_gsum_bytes(const moe_args* a, long cap) {
+  if (a->wfmt != MOE_W_INT4_G128 || moe::int4_decode(a->T, a->top_k, a->E, a->H, a->I)) return 0;
+  return align_up(static_cast<size_t>(cap) * (a->I / 128) * 4);
+}
+
 // Workspace layout for validated sizes (T may be 0).
 moe_ws_layout make_layout(const moe_args* a) {
   moe_ws_layout L;
@@ -107,6 +114,7 @@ moe_ws_layout make_layout(const moe_args* a) {
   L.y = take(static_cast<size_t>(cap) * a->H * (moe::y_is_f32(a->wfmt) ? 4 : 2));
   L.permute_ws = take(moe::permute_workspace_bytes(a->T, a->top_k, a->E));
   L.router_ws = a->w_router ? take(moe::router_workspace_bytes(a->T, a->H, a->E)) : -1;
+  take(int4_gsum_bytes(a, cap));  // at the layout's end
   L.total = static_cast<int64_t>(off);
   return L;
 }
@@ -277,10 +285,15 @@ moe_status run_layer(const moe_args* a, void* ws, size_t ws_bytes, hipEvent_t* e
   g.x_scale = nullptr;
   g.x_mx = nullptr;
   g.x_gsum = nullptr;
+  g.inter_gsum = nullptr;
   if (!mark(2)) return MOE_ERR_HIP;
   if (a->wfmt == MOE_W_INT4_G128 && !moe::int4_decode(a->T, a->top_k, a->E, a->H, a->I)) {
+    // the reordered hidden rows (T*H bf16) lie in y's region (cap >= T rows of
+    // H fp32), which is written only after GEMM1 has read them
     float* gs = at<float>(ws, L.act_s);
-    if (moe::launch_group_sum(a->hidden, a->T, a->H, gs, stream) != hipSuccess) return MOE_ERR_HIP;
+    uint16_t* xp = at<uint16_t>(ws, L.y);
+    if (moe::launch_group_sum(a->hidden, a->T, a->H, gs, xp, nullptr, stream) != hipSuccess) return MOE_ERR_HIP;
+    g.x = xp;
     g.x_gsum = gs;
   }
   if (a->wfmt == MOE_W_FP8E4M3_B128) {
@@ -317,6 +330,13 @@ moe_status run_layer(const moe_args* a, void* ws, size_t ws_bytes, hipEvent_t* e
   if (!mark(3)) return MOE_ERR_HIP;
   if (moe::launch_gemm1(a->wfmt, g, stream) != hipSuccess) return MOE_ERR_HIP;
   if (!mark(4)) return MOE_ERR_HIP;
+  if (g.x_gsum) {  // tiled int4
+    float* gs = at<float>(ws, L.total - static_cast<int64_t>(int4_gsum_bytes(a, L.cap)));
+    if (moe::launch_group_sum(static_cast<const uint16_t*>(g.inter), L.cap, a->I, gs, nullptr, offs + a->E, stream) !=
+        hipSuccess)
+      return MOE_ERR_HIP;
+    g.inter_gsum = gs;
+  }
   if (moe::launch_gemm2(a->wfmt, g, stream) != hipSuccess) return MOE_ERR_HIP;
   if (!mark(5)) return MOE_ERR_HIP;
   if (moe::launch_combine(g.y, moe::y_is_f32(a->wfmt), wts, inv, a->T, a->H, a->top_k,
@@ -333,7 +353,11 @@ moe_status run_layer(const moe_args* a, void* ws, size_t ws_bytes, hipEvent_t* e
 // process ends.  In host code `scratch` names a host-side stand-in, never the
 // device memory: its device address is looked up once per device and only
 // that address is used.
-static __device__ __align__(256) uint8_t scratch[MOE_STATIC_WS_BYTES];
+// MOE_STATIC_WS_BYTES limits a layer's workspace without the int4 group sums at
+// its end; these are at most 1/64 of it (the intermediate's share) and have
+// their own room.
+constexpr size_t kStaticWsBytes = MOE_STATIC_WS_BYTES + MOE_STATIC_WS_BYTES / 64 + 256;
+static __device__ __align__(256) uint8_t scratch[kStaticWsBytes];
 
 namespace {
 
@@ -370,10 +394,11 @@ moe_status moe_forward_static_ws(const moe_args* a, hipStream_t stream) {
   moe_status st = check_args(a);
   if (st != MOE_OK) return st;
   if (a->T == 0) return MOE_OK;
-  if (static_cast<size_t>(make_layout(a).total) > MOE_STATIC_WS_BYTES) return MOE_ERR_WORKSPACE;
+  const moe_ws_layout L = make_layout(a);
+  if (static_cast<size_t>(L.total) - int4_gsum_bytes(a, L.cap) > MOE_STATIC_WS_BYTES) return MOE_ERR_WORKSPACE;
   void* ws = scratch_on_current_device();
   if (!ws) return MOE_ERR_HIP;
-  return run_layer(a, ws, MOE_STATIC_WS_BYTES, nullptr, stream);
+  return run_layer(a, ws, kStaticWsBytes, nullptr, stream);
 }
 
 moe_status moe_forward_profiled(const moe_args* a, void* ws, size_t ws_bytes,

@@ -239,6 +239,23 @@ def test_int4_zero_and_wide_scales(dev):
     _check(cfg, inp=out)
 
 
+@pytest.mark.parametrize("T,H,I", [(70, 512, 128),     # K of the second product one step
+                                   (33, 640, 384),     # 128-column tiles of the second product
+                                   (300, 1280, 1152)])  # tiles whose second row block is all pads, and full ones
+def test_int4_tiled_second_product(dev, T, H, I):
+    # The oracle rounds the intermediate to bf16 where the layer does; codes
+    # and scales are exact here, so what is left is fp32 sums (under 2^-17 of
+    # the result over these K) and the intermediate values they tip to the
+    # other bf16 neighbour (2^-8 of a value, a few in a hundred of them: under
+    # 2^-11 in the 2-norm).  A bf16 rounding of q * scale alone adds 2^-9.8.
+    cfg = synth.tiny_config(5, T=T, H=H, I=I, E=6, top_k=2)
+    inp = _scale_blocks(synth.make_inputs(cfg), cfg.wfmt, seed=T)
+    out, ref, L = check_forward(cfg, inp)
+    assert L["block_m"] == 64
+    rel = np.linalg.norm(out - ref["out"]) / np.linalg.norm(ref["out"])
+    assert rel <= 2.0 ** -11, rel
+
+
 # ---- int4 decode route: the 16-row streamed kernels up to 8 routed rows per
 # expert on average; both products sum each 128-group of codes exactly and
 # apply the row's group scale to the group's partial in fp32
