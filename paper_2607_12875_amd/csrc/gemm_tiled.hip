@@ -39,6 +39,7 @@
 // number of real row tiles is read on the device from expert_offsets[E]
 // (segments are padded to BM).
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 #include "launch.hpp"
@@ -500,6 +501,24 @@ void moe_gemm_tiled(GroupedGemm g) {
 #define brow(j) (GEMM1 ? ((j) < TN / 2 ? wn * (WTN / 2) + (j) * 32 : NC + wn * (WTN / 2) + ((j) - TN / 2) * 32) \
                        : wn * WTN + (j) * 32)
 
+    // Row blocks (of 32) of the tile that hold routed rows: the last tile of an
+    // expert is padded, on average by half a tile, and the split bf16 and
+    // MXFP4 loops below, which the matrix pipe's time bounds, leave the blocks
+    // of pads out (every wave holds all BM rows, so all gain alike).  Layer
+    // before and after: bf16, 4096 x 1408 x 64 experts, top 6, 4096 tokens 1198
+    // and 1181 us, 777 tokens 506 and 498; MXFP4, 7168 x 2048 x 256 experts,
+    // top 8, 8192 tokens 6392 and 6180 us.  The fp8 and MXFP8 products, bound
+    // by their copies, keep 2 x 2 waves.
+    constexpr bool SKIP = NP > 0 && (FMT == 0 || FMT == 4);
+    static_assert(!SKIP || (WM == 1 && TM == 4), "four row blocks per wave");
+    int nb = TM;
+    if constexpr (SKIP) nb = __popcll(__ballot(lane < TM && g.sorted_ids[m0 + 32 * (lane % TM)] < g.n_routed));
+    auto for_blocks = [&](auto loop) {
+      if (nb >= 4) loop(std::integral_constant<int, 4>{});
+      else if (nb == 3) loop(std::integral_constant<int, 3>{});
+      else if (nb == 2) loop(std::integral_constant<int, 2>{});
+      else loop(std::integral_constant<int, 1>{});
+    };
     if constexpr (NP > 0 && FMT == 0) {
       // Math waves of a split bf16 launch: fragments are read one MFMA K
       // substep ahead into a double buffer.  The barrier for stage kt+1 sits
@@ -508,47 +527,160 @@ void moe_gemm_tiled(GroupedGemm g) {
       // while those MFMAs run; the barrier count is still one per step.
       constexpr int NKK = KE / 16;
       static_assert(NKK % 2 == 0, "substep parity");
-      bf16x8 fa[2][TM], fb[2][TN];
-      auto read_frags = [&](int kt, int kk, int buf) {
-        const uint8_t* As = &smem[(sb + kt) % STAGES][0];
-        const uint8_t* Bs = As + A_BYTES;
-        const int ch = 2 * kk + kg;
+      for_blocks([&](auto nbc) {
+        constexpr int NB = decltype(nbc)::value;
+        bf16x8 fa[2][NB], fb[2][TN];
+        auto read_frags = [&](int kt, int kk, int buf) {
+          const uint8_t* As = &smem[(sb + kt) % STAGES][0];
+          const uint8_t* Bs = As + A_BYTES;
+          const int ch = 2 * kk + kg;
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          const int r = wm * WTM + i * 32 + l32;
-          fa[buf][i] = as_bf16x8(ld16(As + r * KB + ((ch ^ swz<KB>(r)) << 4)));
-        }
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const int r = brow(j) + l32;
-          fb[buf][j] = as_bf16x8(ld16(Bs + r * BB + ((ch ^ swz<KB>(r)) << 4)));
-        }
-      };
-      bar();  // stage 0 has landed
-      read_frags(0, 0, 0);
-      for (int kt = 0; kt < nk; ++kt) {
-#pragma unroll
-        for (int kk = 0; kk < NKK; ++kk) {
-          if (kk + 1 < NKK) {
-            read_frags(kt, kk + 1, (kk + 1) & 1);
-          } else if (kt + 1 < nk) {
-            __atomic_signal_fence(__ATOMIC_SEQ_CST);
-            lds_wait();  // stage kt is in registers
-            bar();                               // stage kt+1 has landed; buffer kt is free
-            read_frags(kt + 1, 0, 0);
+          for (int i = 0; i < NB; ++i) {
+            const int r = wm * WTM + i * 32 + l32;
+            fa[buf][i] = as_bf16x8(ld16(As + r * KB + ((ch ^ swz<KB>(r)) << 4)));
           }
-          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int i = 0; i < TM; ++i)
+          for (int j = 0; j < TN; ++j) {
+            const int r = brow(j) + l32;
+            fb[buf][j] = as_bf16x8(ld16(Bs + r * BB + ((ch ^ swz<KB>(r)) << 4)));
+          }
+        };
+        bar();  // stage 0 has landed
+        read_frags(0, 0, 0);
+        for (int kt = 0; kt < nk; ++kt) {
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-              acc[i][j] = TRB ? mfma32x32x16(fb[kk & 1][j], fa[kk & 1][i], acc[i][j])
-                              : mfma32x32x16(fa[kk & 1][i], fb[kk & 1][j], acc[i][j]);
-          __builtin_amdgcn_sched_barrier(0);
+          for (int kk = 0; kk < NKK; ++kk) {
+            if (kk + 1 < NKK) {
+              read_frags(kt, kk + 1, (kk + 1) & 1);
+            } else if (kt + 1 < nk) {
+              __atomic_signal_fence(__ATOMIC_SEQ_CST);
+              lds_wait();  // stage kt is in registers
+              bar();                               // stage kt+1 has landed; buffer kt is free
+              read_frags(kt + 1, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+              for (int j = 0; j < TN; ++j)
+                acc[i][j] = TRB ? mfma32x32x16(fb[kk & 1][j], fa[kk & 1][i], acc[i][j])
+                                : mfma32x32x16(fa[kk & 1][i], fb[kk & 1][j], acc[i][j]);
+            __builtin_amdgcn_sched_barrier(0);
+          }
         }
-      }
+      });
     }
-    for (int kt = 0; kt < nk && !(NP > 0 && FMT == 0); ++kt) {
+    if constexpr (NP > 0 && FMT == 4) {
+      // Math waves of a split MXFP4 launch.  One math wave per SIMD issues in
+      // order, so decoding a substep's weights and then multiplying them ran
+      // the VALU (its conversions) and the matrix pipe one after the
+      // other.  Here the next substep's conversions are interleaved with this
+      // substep's MFMAs; fragments are read one substep
+      // ahead, and the barrier for stage kt+1 sits before the last substep's
+      // MFMAs as in the bf16 loop above.
+      // Lane group kg covers elements [64 kg, 64 kg + 64) of the step, the
+      // 32-element blocks 2 kg and 2 kg + 1: their E8M0 bytes are bytes
+      // 2 kg and 2 kg + 1 of the row's scale dword, passed as float(s << 23).
+      constexpr int NKK = KE / 16;
+      static_assert(NKK == 8, "two 32-element blocks per lane group, four substeps each");
+      for_blocks([&](auto nbc) {
+        constexpr int NB = decltype(nbc)::value;
+        bf16x8 fa[2][NB], fb[2][TN];
+        u32x4 bw[2][TN];  // [block][column tile]
+        uint32_t sd[TN];  // this lane group's two scale bytes
+        float sc[2][TN];
+        auto stage = [&](int kt) { return &smem[(sb + kt) % STAGES][0]; };
+        auto read_a = [&](int kt, int kk, int buf) {
+          const uint8_t* As = stage(kt);
+          const int ch = NKK * kg + kk;
+#pragma unroll
+          for (int i = 0; i < NB; ++i) {
+            const int r = wm * WTM + i * 32 + l32;
+            fa[buf][i] = as_bf16x8(ld16(As + r * KB + ((ch ^ swz<KB>(r)) << 4)));
+          }
+        };
+        auto read_w = [&](int kt, int h) {
+          const uint8_t* Bs = stage(kt) + A_BYTES;
+#pragma unroll
+          for (int j = 0; j < TN; ++j) {
+            const int r = brow(j) + l32;
+            bw[h][j] = ld16(Bs + r * BB + (((2 * kg + h) ^ swz_b<BB>(r)) << 4));
+          }
+        };
+        auto read_s = [&](int kt) {
+          const uint32_t* sW = reinterpret_cast<const uint32_t*>(stage(kt) + A_BYTES + B_BYTES);
+#pragma unroll
+          for (int j = 0; j < TN; ++j) sd[j] = sW[brow(j) + l32];
+        };
+        auto scales = [&]() {
+#pragma unroll
+          for (int j = 0; j < TN; ++j) {
+            sc[0][j] = __uint_as_float((sd[j] >> (16 * kg) & 0xFFu) << 23);
+            sc[1][j] = __uint_as_float((sd[j] >> (16 * kg + 8) & 0xFFu) << 23);
+          }
+        };
+        auto decode = [&](int kk, int j, int buf) {
+          fb[buf][j] = as_bf16x8(mxfp4x8_to_bf16(bw[kk / 4][j][kk % 4], sc[kk / 4][j]));
+        };
+        bar();  // stage 0 has landed
+        read_s(0);
+        read_w(0, 0);
+        read_a(0, 0, 0);
+        scales();
+#pragma unroll
+        for (int j = 0; j < TN; ++j) decode(0, j, 0);
+        // the last step stands apart: a branch around its missing barrier would
+        // let the compiler sink the earlier substeps' MFMAs past it
+        auto step = [&](int kt, auto last) {
+#pragma unroll
+          for (int kk = 0; kk < NKK; ++kk) {
+            const bool more = kk + 1 < NKK || !decltype(last)::value;  // a later substep follows
+            if (kk + 1 < NKK) {
+              if (kk == 0) read_w(kt, 1);
+              read_a(kt, kk + 1, (kk + 1) & 1);
+            } else if (more) {
+              __atomic_signal_fence(__ATOMIC_SEQ_CST);
+              lds_wait();  // stage kt is in registers
+              bar();       // stage kt+1 has landed; buffer kt is free
+              read_s(kt + 1);
+              read_w(kt + 1, 0);
+              read_a(kt + 1, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (more) {
+              if (kk + 1 == NKK) scales();
+#pragma unroll
+              for (int j = 0; j < TN; ++j) decode((kk + 1) % NKK, j, (kk + 1) & 1);
+            }
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+              for (int j = 0; j < TN; ++j)
+                acc[i][j] = TRB ? mfma32x32x16(fb[kk & 1][j], fa[kk & 1][i], acc[i][j])
+                                : mfma32x32x16(fa[kk & 1][i], fb[kk & 1][j], acc[i][j]);
+            if (kk + 1 < NKK) {
+#pragma unroll
+              for (int q = 0; q < NB * TN; ++q) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, (4 + NB - 1) / NB, 0);
+              }
+            } else if (more) {
+              // the next stage's words arrive under the first half of the MFMAs
+              __builtin_amdgcn_sched_group_barrier(0x008, NB * TN / 2, 0);
+#pragma unroll
+              for (int q = 0; q < NB * TN / 2; ++q) {
+                __builtin_amdgcn_sched_group_barrier(0x002, (8 + NB - 1) / NB + 4, 0);
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+              }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        };
+        for (int kt = 0; kt + 1 < nk; ++kt) step(kt, std::false_type{});
+        step(nk - 1, std::true_type{});
+      });
+    }
+    for (int kt = 0; kt < nk && !(NP > 0 && (FMT == 0 || FMT == 4)); ++kt) {
       if constexpr (NP == 0) wait_ahead(min(STAGES - 2, nk - 1 - kt));
       bar();  // every stage-kt copy of every copy wave has landed
       const bool pre = NP == 0 && kt + STAGES - 1 < nk;  // this wave starts a later stage
@@ -853,48 +985,6 @@ void moe_gemm_tiled(GroupedGemm g) {
 #pragma unroll
             for (int j = 0; j < TN; ++j) acc[i][j] = mfma32x32x64_f4f8<2>(bq[1][j], af[1][i], db[j], da[i], acc[i][j]);
         }
-      } else {  // MXFP4
-        // lane group kg covers elements [64 kg, 64 kg + 64) of the step, the
-        // 32-element blocks 2 kg and 2 kg + 1: their E8M0 bytes are bytes
-        // 2 kg and 2 kg + 1 of the row's scale dword, passed as float(s << 23)
-        constexpr int NKK = KE / 16, NBW = NKK / 4;
-        static_assert(NBW == 2, "one 16-byte chunk per 32-element block");
-        const uint32_t* sW = reinterpret_cast<const uint32_t*>(Ss);  // one dword per tile row
-        float sc[TN][NBW];
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const uint32_t d = sW[brow(j) + l32];
-#pragma unroll
-          for (int h = 0; h < NBW; ++h) sc[j][h] = __uint_as_float(((d >> (8 * (NBW * kg + h))) & 0xFFu) << 23);
-        }
-#pragma unroll
-        for (int h = 0; h < NBW; ++h) {
-          u32x4 bw[TN];
-#pragma unroll
-          for (int j = 0; j < TN; ++j) {
-            const int r = brow(j) + l32;
-            bw[j] = ld16(Bs + r * BB + (((NBW * kg + h) ^ swz_b<BB>(r)) << 4));
-          }
-#pragma unroll
-          for (int k4 = 0; k4 < 4; ++k4) {
-            const int kk = 4 * h + k4, ch = NKK * kg + kk;
-            bf16x8 a[TM], b[TN];
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-              const int r = wm * WTM + i * 32 + l32;
-              a[i] = as_bf16x8(ld16(As + r * KB + ((ch ^ swz<KB>(r)) << 4)));
-            }
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-              const uint32_t wd = k4 == 0 ? bw[j].x : (k4 == 1 ? bw[j].y : (k4 == 2 ? bw[j].z : bw[j].w));
-              b[j] = as_bf16x8(mxfp4x8_to_bf16(wd, sc[j][h]));
-            }
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-              for (int j = 0; j < TN; ++j) acc[i][j] = TRB ? mfma32x32x16(b[j], a[i], acc[i][j]) : mfma32x32x16(a[i], b[j], acc[i][j]);
-          }
-        }
       }
     }
 #undef brow
@@ -1000,7 +1090,8 @@ void moe_gemm_tiled(GroupedGemm g) {
         uint16_t* o = static_cast<uint16_t*>(g.inter);
         auto store = [&](bool masked) {
 #pragma unroll
-          for (int i = 0; i < TM; ++i)
+          for (int i = 0; i < TM; ++i) {
+            if (i >= nb) break;  // blocks of pads are never read
 #pragma unroll
             for (int j = 0; j < TH; ++j)
 #pragma unroll
@@ -1011,6 +1102,7 @@ void moe_gemm_tiled(GroupedGemm g) {
                 const int col = n0 + wn * (WTN / 2) + j * 32 + lc;
                 if (!masked || col < g.I) o[static_cast<size_t>(row) * g.I + col] = f32_to_bf16(av[i][j][v]);
               }
+          }
         };
         if (n0 + NC <= g.I) store(false);  // uniform: only a ragged last column tile masks
         else store(true);
@@ -1131,13 +1223,13 @@ hipError_t launch_tiled(const GroupedGemm& g, hipStream_t s) {
 // bf16 tile shapes: rows x weight rows per workgroup, waves as WM x WN.
 #ifndef MOE_T1_BNW
 #define MOE_T1_BNW 256
-#define MOE_T1_WM 2
-#define MOE_T1_WN 2
+#define MOE_T1_WM 1
+#define MOE_T1_WN 4
 #endif
 #ifndef MOE_T2_BNW
 #define MOE_T2_BNW 256
-#define MOE_T2_WM 2
-#define MOE_T2_WN 2
+#define MOE_T2_WM 1
+#define MOE_T2_WN 4
 #endif
 #ifndef MOE_TBF_BM
 #define MOE_TBF_BM 128
@@ -1230,15 +1322,15 @@ hipError_t launch_gemm1_mxfp4_tiled(const GroupedGemm& g, hipStream_t s) {
   if constexpr (MOE_TMX_BM == 64)
     return launch_tiled<4, true, 64, 256, 1, 4, MOE_TGM_INT4, MOE_TI4_KB, MOE_TI4_STAGES, MOE_TI4_NP1>(g, s);
   else
-    return launch_tiled<4, true, 128, 256, 2, 2, MOE_TGM, 256, 3, 4>(g, s);
+    return launch_tiled<4, true, 128, 256, 1, 4, MOE_TGM, 256, 3, 4>(g, s);
 }
 hipError_t launch_gemm2_mxfp4_tiled(const GroupedGemm& g, hipStream_t s) {
   if constexpr (MOE_TMX_BM == 64) {
     if (g.H % 256) return launch_tiled<4, false, 64, 128, 1, 4, MOE_TGM_INT4, MOE_TI4_KB, MOE_TI4_STAGES, MOE_TI4_NP2>(g, s);
     return launch_tiled<4, false, 64, 256, 1, 4, MOE_TGM_INT4, MOE_TI4_KB, MOE_TI4_STAGES, MOE_TI4_NP2>(g, s);
   } else {
-    if (g.H % 256) return launch_tiled<4, false, 128, 128, 2, 2, MOE_TGM, 256, 3, 4>(g, s);
-    return launch_tiled<4, false, 128, 256, 2, 2, MOE_TGM, 256, 3, 4>(g, s);
+    if (g.H % 256) return launch_tiled<4, false, 128, 128, 1, 4, MOE_TGM, 256, 3, 4>(g, s);
+    return launch_tiled<4, false, 128, 256, 1, 4, MOE_TGM, 256, 3, 4>(g, s);
   }
 }
 // MXFP4 weights x MXFP8 activations: the fp8 tile (128 x 256, four math

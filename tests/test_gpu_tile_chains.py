@@ -6,6 +6,7 @@ the point where the next tile's first steps stop being issued together
 with the current tile's last step and start being issued in stride: 5
 steps (issued together) and 6 steps (in stride) with three stages, and a
 four-stage kernel (MXFP8 activations, 128-element steps) with 9 steps."""
+import numpy as np
 import pytest
 
 import synth
@@ -28,3 +29,18 @@ def test_mxfp8_four_stage_chained_tiles(dev):
     # I = 1152 is a multiple of 128 but not of 256: the second product takes
     # 128-element steps on the four-stage kernel, 9 per tile
     check_forward(synth.tiny_config(9, T=600, H=4096, E=16, I=1152, top_k=4))
+
+
+@pytest.mark.parametrize("n,H,I", [(3, 512, 136), (8, 512, 256), (8, 384, 128)])
+def test_padded_row_blocks(dev, n, H, I):
+    # bf16 (ragged K and columns too) and MXFP4 tiles with one to four live
+    # 32-row blocks, on either side of each boundary: every token picks expert
+    # e with probability falling in e, so segment lengths spread over the tile;
+    # the routed rows are counted to be sure
+    cfg = synth.tiny_config(n, T=700, H=H, I=I, E=16, top_k=2)
+    inp = synth.make_inputs(cfg)
+    lg = np.random.default_rng(3).gumbel(size=(700, 16)) + np.log(np.arange(16, 0, -1) ** 1.5)
+    _, ref, L = check_forward(cfg, dict(inp, logits=lg.astype(np.float32)))
+    assert L["block_m"] == 128
+    live = {-(-int(c % 128) // 32) or 4 for c in np.bincount(ref["ids"].ravel(), minlength=16) if c}
+    assert live == {1, 2, 3, 4}, live
