@@ -40,7 +40,8 @@ def test_padded_row_blocks(dev, n, H, I):
     cfg = synth.tiny_config(n, T=700, H=H, I=I, E=16, top_k=2)
     inp = synth.make_inputs(cfg)
     lg = np.random.default_rng(3).gumbel(size=(700, 16)) + np.log(np.arange(16, 0, -1) ** 1.5)
-    _, ref, L = check_forward(cfg, dict(inp, logits=lg.astype(np.float32)))
+    bias = None if inp["sel_bias"] is None else np.zeros_like(inp["sel_bias"])
+    _, ref, L = check_forward(cfg, dict(inp, logits=(lg / 4).astype(np.float32), sel_bias=bias))
     assert L["block_m"] == 128
     live = {-(-int(c % 128) // 32) or 4 for c in np.bincount(ref["ids"].ravel(), minlength=16) if c}
     assert live == {1, 2, 3, 4}, live
