@@ -77,7 +77,7 @@ __device__ __forceinline__ bf16x8 int4x8_biased_bf16(uint32_t w, uint32_t mask) 
 // 256-byte row spans all 64 banks, so there the slot alone must tell 16
 // consecutive rows apart: r & 15.
 template <int KB>
-__device__ __forceinline__ int swz(int r) { return KB == 256 ? r & 15 : KB == 128 ? (r >> 1) & 7 : (r >> 2) & 3; }
+__device__ __forceinline__ int swz(int r) { return KB >= 256 ? r & 15 : KB == 128 ? (r >> 1) & 7 : (r >> 2) & 3; }
 // int4 B rows (32 or 64 bytes: 2 or 4 chunks)
 // (128-byte 4-bit rows, 256-element MXFP8 steps: as swz<128>)
 template <int BB>
@@ -89,7 +89,7 @@ __device__ __forceinline__ int swz_b(int r) { return BB == 32 ? (r >> 2) & 1 : B
 // instruction.  NP == 0: the math waves issue the copies themselves.
 template <int FMT, bool GEMM1, int BM, int BNW, int WM, int WN, int GM, int KBT = 128, int STAGES = 3, int NP = 0>
 // The 64-row 4-bit GEMMs with copy waves are held to 128 registers, which keeps two workgroups per CU.
-__global__ __launch_bounds__((WM * WN + NP) * 64) __attribute__((amdgpu_waves_per_eu((FMT == 2 || FMT == 4) && (GEMM1 || NP > 0) && BM == 64 ? 4 : 1)))
+__global__ __launch_bounds__((WM * WN + NP) * 64) __attribute__((amdgpu_waves_per_eu((FMT == 2 || FMT == 4) && (GEMM1 || NP > 0) && BM == 64 && KBT < 512 ? 4 : 1)))
 void moe_gemm_tiled(GroupedGemm g) {
   constexpr int NW = WM * WN, NT = (NW + NP) * 64;
   constexpr int LW = NP > 0 ? NP : NW;  // waves that issue the copies
@@ -100,8 +100,8 @@ void moe_gemm_tiled(GroupedGemm g) {
   constexpr bool MX8 = FMT == 5;              // MXFP4 weights, MXFP8 activations
   constexpr bool A8 = FMT == 1 || MX8;        // one-byte (e4m3) activations
   constexpr bool B4 = F4B || MX8;             // 4-bit weight rows
-  static_assert(KBT == 128 || (KBT == 64 && FMT == 0) || (KBT == 256 && (F4B || FMT == 5)),
-                "64-byte steps are bf16 only, 256-byte steps 4-bit weights only");
+  static_assert(KBT == 128 || (KBT == 64 && FMT == 0) || (KBT == 256 && (F4B || FMT == 5)) || (KBT == 512 && FMT == 2 && NP > 0),
+                "64-byte steps are bf16 only, 256-byte steps 4-bit weights only, 512-byte steps int4 only");
   constexpr int KB = KBT;                                       // A bytes per row per step
   constexpr int KE = A8 ? KB : KB / 2;                                 // K elements per step
   constexpr int BB = B4 ? KE / 2 : KB;                                 // B bytes per row per step
@@ -129,12 +129,13 @@ void moe_gemm_tiled(GroupedGemm g) {
   // row group g), then MXD BNW/64 slots of the B rows' likewise; slots past
   // those load a harmless dummy.
   constexpr bool GSUM = FMT == 2;
+  constexpr int GD = GSUM ? KE / 128 : 1;  // int4: scale groups per step
   constexpr int MXD = MX8 ? KE / 128 : 1;
   constexpr int NSLOT = FMT == 0 ? 0 : (MX8 ? MXD * (BM + BNW) / 64 : (GSUM ? 2 : 1) * NW);
   constexpr int SC = (NSLOT + LW - 1) / LW;  // scale loads per copy wave per stage
   static_assert(FMT != 1 || BM / 64 < NW, "fp8 scale DMA layout");
   static_assert(!F4B || (NW == 4 && BNW / 64 <= NW), "4-bit scale DMA layout");
-  static_assert(!GSUM || (BNW / 64 + BM / 64 <= 2 * NW && STAGES == 2), "int4 group-sum DMA layout");
+  static_assert(!GSUM || (BNW / 64 + GD * BM / 64 <= 2 * NW && STAGES == 2), "int4 group-sum DMA layout");
   static_assert(STAGES >= 2 && (STAGES - 2) * (A_CH + B_CH + SC) < 64, "vmcnt range");
   constexpr int A_BYTES = BM * KB, B_BYTES = BNW * BB, S_BYTES = SC * LW * 256;
   constexpr int STAGE = A_BYTES + B_BYTES + S_BYTES;
@@ -226,8 +227,8 @@ void moe_gemm_tiled(GroupedGemm g) {
           if constexpr (NP > 0) v = staged ? lds_sid[lw][ra] : g.sorted_ids[m0 + ra];
           else v = g.sorted_ids[m0 + ra];
         }
-        const int rg = (lw + k * LW - BNW / 64) * 64 + lane;  // group-sum slot row
-        if (GSUM && lw + k * LW >= BNW / 64 && lw + k * LW < BNW / 64 + BM / 64) {
+        const int rg = (lw + k * LW - BNW / 64) % (BM / 64) * 64 + lane;  // group-sum slot row
+        if (GSUM && lw + k * LW >= BNW / 64 && lw + k * LW < BNW / 64 + GD * BM / 64) {
           if constexpr (NP > 0) v = staged ? lds_sid[lw][rg] : g.sorted_ids[m0 + rg];
           else v = g.sorted_ids[m0 + rg];
         }
@@ -300,11 +301,13 @@ void moe_gemm_tiled(GroupedGemm g) {
           src.s[k] = reinterpret_cast<const uint8_t*>(static_cast<const uint16_t*>(GEMM1 ? g.w1_scale : g.w2_scale) +
                                                       (static_cast<size_t>(e) * (GEMM1 ? 2 * g.I : g.H) + n) * (K / 128));
           src.ss[k] = 1;  // advanced per step in elements below
-        } else if (GSUM && sl < BNW / 64 + BM / 64) {
-          // row (sl - BNW/64)*64 + lane: its sum over K step kt's group, one float per step
-          if (GEMM1) src.s[k] = reinterpret_cast<const uint8_t*>(g.x_gsum + token(sid[A_CH + k]) * (g.H / 128));
-          else src.s[k] = reinterpret_cast<const uint8_t*>(g.inter_gsum + static_cast<size_t>(m0 + (sl - BNW / 64) * 64 + lane) * (g.I / 128));
-          src.ss[k] = 4;
+        } else if (GSUM && sl < BNW / 64 + GD * BM / 64) {
+          // tile row (sl - BNW/64) % (BM/64) * 64 + lane: its sum over the
+          // step's group (sl - BNW/64) / (BM/64), GD floats per step
+          const int d = (sl - BNW / 64) / (BM / 64), r = (sl - BNW / 64) % (BM / 64) * 64 + lane;
+          if (GEMM1) src.s[k] = reinterpret_cast<const uint8_t*>(g.x_gsum + token(sid[A_CH + k]) * (g.H / 128) + d);
+          else src.s[k] = reinterpret_cast<const uint8_t*>(g.inter_gsum + static_cast<size_t>(m0 + r) * (g.I / 128) + d);
+          src.ss[k] = 4 * GD;
         }
       } else if constexpr (MX8) {
         if (sl < MXD * (BM / 64)) {
@@ -376,7 +379,7 @@ void moe_gemm_tiled(GroupedGemm g) {
       } else if constexpr (FMT == 2) {
         // B scale words (ss 1): element kt*KE/128 of the row, rounded down to
         // an even element (4-byte aligned); group sums advance one float per
-        // step (ss 4); dummies stay put (ss 0)
+        // group (ss 4 GD); dummies stay put (ss 0)
         const uint8_t* p = src.s[k] + kt * src.ss[k];
         if (src.ss[k] == 1) {
           const uintptr_t a = reinterpret_cast<uintptr_t>(src.s[k]) + ((kt * KE) / 128) * 2;
@@ -509,13 +512,14 @@ void moe_gemm_tiled(GroupedGemm g) {
     // and 1181 us, 777 tokens 506 and 498; MXFP4, 7168 x 2048 x 256 experts,
     // top 8, 8192 tokens 6392 and 6180 us.  The fp8 and MXFP8 products, bound
     // by their copies, keep 2 x 2 waves.
-    constexpr bool SKIP = NP > 0 && (FMT == 0 || FMT == 4);
-    static_assert(!SKIP || (WM == 1 && TM == 4), "four row blocks per wave");
+    constexpr bool I4P = FMT == 2 && KB == 512;  // int4 on the software-pipelined loop
+    constexpr bool SKIP = NP > 0 && (FMT == 0 || FMT == 4 || I4P);
+    static_assert(!SKIP || (WM == 1 && (TM == 4 || TM == 2)), "every wave holds all row blocks");
     int nb = TM;
     if constexpr (SKIP) nb = __popcll(__ballot(lane < TM && g.sorted_ids[m0 + 32 * (lane % TM)] < g.n_routed));
     auto for_blocks = [&](auto loop) {
-      if (nb >= 4) loop(std::integral_constant<int, 4>{});
-      else if (nb == 3) loop(std::integral_constant<int, 3>{});
+      if (TM >= 4 && nb >= 4) loop(std::integral_constant<int, TM >= 4 ? 4 : 1>{});
+      else if (TM >= 4 && nb == 3) loop(std::integral_constant<int, TM >= 4 ? 3 : 1>{});
       else if (nb == 2) loop(std::integral_constant<int, 2>{});
       else loop(std::integral_constant<int, 1>{});
     };
@@ -680,7 +684,135 @@ void moe_gemm_tiled(GroupedGemm g) {
         step(nk - 1, std::true_type{});
       });
     }
-    for (int kt = 0; kt < nk && !(NP > 0 && (FMT == 0 || FMT == 4)); ++kt) {
+    if constexpr (I4P) {
+      // int4, 256 K elements (two scale groups) per step, so every weight row
+      // gives a whole 128-byte line: the number of lines through the vector
+      // L1 set the time of the 128-element steps below, which ask for half
+      // lines.  The stages leave room for one workgroup per CU, one math wave
+      // per SIMD, so the next substep's decode and the group's rescale are
+      // interleaved with the MFMAs.  The arithmetic is that of the
+      // 128-element loop below.  512 tokens, 4096 x 1536 x 128 experts, top 8:
+      // the layer 388 us with the 128-element steps, 365 with these.
+      // Substep t: K elements [128 (t/8) + 64 kg + 8 (t%8), +8) of the step,
+      // chunk 16 (t/8) + 8 kg + t%8 of an activation row, word t%4 of chunk
+      // t/4 + 2 kg + 2 (t/8) of a weight row.
+      for_blocks([&](auto nbc) {
+        constexpr int NB = decltype(nbc)::value;
+        static_assert(STAGE % 512 == 0 && A_BYTES % 512 == 0, "rows aligned to their bytes");
+        bf16x8 fa[2][NB], fb[2][TN];
+        u32x4 bw[2][TN];
+        uint32_t sd[TN], keep[TN];
+        float ratio[TN];
+        f32x16 rs[NB];
+        const int ra = l32, rb = brow(0) + l32;
+        const uint32_t oa = ra * KB + (((8 * kg) ^ swz<KB>(ra)) << 4);
+        const uint32_t ob = A_BYTES + rb * BB + (((2 * kg) ^ swz_b<BB>(rb)) << 4);
+        auto stage = [&](int kt) { return smem0 + ((sb + kt) % STAGES) * STAGE; };
+        auto read_a = [&](int kt, int t, int buf) {
+          const uint32_t pa = stage(kt) + oa;
+#pragma unroll
+          for (int i = 0; i < NB; ++i)
+            fa[buf][i] = as_bf16x8(lds16((pa ^ (16 * (t / 8) + t % 8) << 4) + i * 32 * KB));
+        };
+        auto read_w = [&](int kt, int h) {  // words of substeps [4 h, 4 h + 4)
+          const uint32_t pb = stage(kt) + ob;
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            bw[h & 1][j] = lds16((pb ^ (4 * (h / 2) + h % 2) << 4) + (brow(j) - brow(0)) * BB);
+        };
+        auto read_s = [&](int kt) {
+          const uint8_t* Ss = &smem[(sb + kt) % STAGES][A_BYTES + B_BYTES];
+#pragma unroll
+          for (int j = 0; j < TN; ++j) sd[j] = reinterpret_cast<const uint32_t*>(Ss)[brow(j) + l32];
+        };
+        auto read_r = [&](int kt, int q) {  // the rows' biased sums over group q
+          const uint32_t sr = stage(kt) + A_BYTES + B_BYTES + (BNW / 64 + q * (BM / 64)) * 256 + 16 * kg;
+#pragma unroll
+          for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int b4 = 0; b4 < 4; ++b4) {
+              const u32x4 v = lds16(sr + i * 128 + b4 * 32);  // rows 32 i + 8 b4 + 4 kg + [0, 4)
+#pragma unroll
+              for (int c = 0; c < 4; ++c) rs[i][4 * b4 + c] = __uint_as_float(v[c]);
+            }
+        };
+        auto scales = [&](int q) {
+#pragma unroll
+          for (int j = 0; j < TN; ++j) {
+            const float sc = __uint_as_float(q ? sd[j] & 0xFFFF0000u : sd[j] << 16);
+            const bool z = sc == 0.f;
+            const float se = z ? seff[j] : sc;
+            ratio[j] = seff[j] == 0.f ? 0.f : seff[j] * __builtin_amdgcn_rcpf(se);
+            seff[j] = se;
+            keep[j] = z ? 0u : 0x000F000Fu;
+          }
+        };
+        auto decode = [&](int t, int buf) {
+#pragma unroll
+          for (int j = 0; j < TN; ++j) fb[buf][j] = int4x8_biased_bf16(bw[t / 4 & 1][j][t % 4], keep[j]);
+        };
+        bar();  // stage 0 has landed
+        read_s(0);
+        read_w(0, 0);
+        read_a(0, 0, 0);
+        read_r(0, 0);
+        scales(0);
+        decode(0, 0);
+        auto step = [&](int kt, auto last) {  // the last step apart, as above
+          constexpr int NT_ = 16;
+#pragma unroll
+          for (int t = 0; t < NT_; ++t) {
+            const bool more = t + 1 < NT_ || !decltype(last)::value;
+            if (t % 8 == 0) {  // the group's rescale, one tile ahead of its first MFMA
+#pragma unroll
+              for (int i = 0; i < NB; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                  for (int v = 0; v < 16; ++v) acc[i][j][v] = fmaf(acc[i][j][v], ratio[j], rs[i][v]);
+            }
+            if (t + 1 < NT_) {
+              read_a(kt, t + 1, (t + 1) & 1);
+              if (t % 4 == 0 && t + 4 < NT_) read_w(kt, t / 4 + 1);
+              if (t == 7) read_r(kt, 1);
+            } else if (more) {
+              __atomic_signal_fence(__ATOMIC_SEQ_CST);
+              lds_wait();  // stage kt is in registers
+              bar();       // stage kt+1 has landed; buffer kt is free
+              read_s(kt + 1);
+              read_w(kt + 1, 0);
+              read_a(kt + 1, 0, 0);
+              read_r(kt + 1, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (more) {
+              if (t % 8 == 7) scales((t + 1) / 8 % 2);
+              decode((t + 1) % NT_, (t + 1) & 1);
+            }
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+              for (int j = 0; j < TN; ++j) acc[i][j] = mfma32x32x16(fa[t & 1][i], fb[t & 1][j], acc[i][j]);
+            if (t + 1 < NT_) {
+#pragma unroll
+              for (int q = 0; q < NB * TN; ++q) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                if (t == 7) __builtin_amdgcn_sched_group_barrier(0x002, (7 + NB - 1) / NB + 6, 0);  // and the next scales
+                else __builtin_amdgcn_sched_group_barrier(0x002, (7 + NB - 1) / NB, 0);
+              }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+              for (int j = 0; j < TN; ++j) asm volatile("" : "+v"(acc[i][j]));  // the products stay in their substep
+          }
+        };
+        for (int kt = 0; kt + 1 < nk; ++kt) step(kt, std::false_type{});
+        step(nk - 1, std::true_type{});
+      });
+    }
+    for (int kt = 0; kt < nk && !SKIP; ++kt) {
       if constexpr (NP == 0) wait_ahead(min(STAGES - 2, nk - 1 - kt));
       bar();  // every stage-kt copy of every copy wave has landed
       const bool pre = NP == 0 && kt + STAGES - 1 < nk;  // this wave starts a later stage
@@ -1310,9 +1442,14 @@ hipError_t launch_gemm2_fp8(const GroupedGemm& g, hipStream_t s) {
 #define MOE_TI4_STAGES 2
 #endif
 int gemm_block_m_int4(int, int, int) { return MOE_TI4_BM; }
-hipError_t launch_gemm1_int4(const GroupedGemm& g, hipStream_t s) {
-  return launch_tiled<2, true, MOE_TI4_BM, 256, 1, 4, MOE_TGM_INT4, MOE_TI4_KB, MOE_TI4_STAGES, MOE_TI4_NP1>(g, s);
+// 256 K elements per step (whole weight lines, one workgroup per CU) where K
+// is a multiple of that, else 128
+template <bool GEMM1, int BNW>
+hipError_t launch_int4(const GroupedGemm& g, hipStream_t s) {
+  if ((GEMM1 ? g.H : g.I) % 256 == 0) return launch_tiled<2, GEMM1, MOE_TI4_BM, BNW, 1, 4, MOE_TGM_INT4, 512, 2, 4>(g, s);
+  return launch_tiled<2, GEMM1, MOE_TI4_BM, BNW, 1, 4, MOE_TGM_INT4, MOE_TI4_KB, MOE_TI4_STAGES, GEMM1 ? MOE_TI4_NP1 : MOE_TI4_NP2>(g, s);
 }
+hipError_t launch_gemm1_int4(const GroupedGemm& g, hipStream_t s) { return launch_int4<true, 256>(g, s); }
 // MXFP4 weights (same 4-bit packing as int4, E8M0 scales per 32)
 #ifndef MOE_TMX_BM
 #define MOE_TMX_BM 128
@@ -1351,8 +1488,8 @@ hipError_t launch_gemm2_mx8(const GroupedGemm& g, hipStream_t s) {
   return launch_mx8<false, 256>(g, s);
 }
 hipError_t launch_gemm2_int4(const GroupedGemm& g, hipStream_t s) {
-  if (g.H % 256) return launch_tiled<2, false, MOE_TI4_BM, 128, 1, 4, MOE_TGM_INT4, MOE_TI4_KB, MOE_TI4_STAGES, MOE_TI4_NP2>(g, s);
-  return launch_tiled<2, false, MOE_TI4_BM, 256, 1, 4, MOE_TGM_INT4, MOE_TI4_KB, MOE_TI4_STAGES, MOE_TI4_NP2>(g, s);
+  if (g.H % 256) return launch_int4<false, 128>(g, s);
+  return launch_int4<false, 256>(g, s);
 }
 
 }  // namespace moe
