@@ -195,6 +195,7 @@ void moe_gemm_tiled(GroupedGemm g) {
     const uint8_t* b[B_CH];  // B rows
     const uint8_t* s[NSL];   // scale words
     int ss[NSL];             // scale advance per step
+    bool once;               // the expert has one row tile: its weight rows are read once (uniform)
   };
   // staged: the tile's BM row ids are in this copy wave's lds_sid slot (else
   // they are read from sorted_ids)
@@ -210,6 +211,15 @@ void moe_gemm_tiled(GroupedGemm g) {
     // copies the zero chunk at every step: one cache line per instruction
     // rather than a row's eight, and zeros in LDS; its products are never
     // read.  Scale sources of pad rows read the last token's.
+    // Weights of an expert with one row tile are read by one workgroup only:
+    // the non-temporal hint keeps them from displacing the rows that other
+    // tiles share in L2 (fp8, 7168 x 2048 x 256 experts, top 8, 300 tokens: the
+    // layer 1257 us without, 1218 with; bf16, 777 tokens 493 and 477; int4, 512
+    // tokens 365 and 359).  With two or more row tiles the hint costs the
+    // sharing (prefill GEMM1 675 -> 973 us with it everywhere).  The 128-element
+    // int4 steps, whose registers are all taken, stay without.
+    constexpr bool ONCE = !(FMT == 2 && KB == 256);
+    src.once = ONCE && __builtin_amdgcn_readfirstlane(lds_off[e + 1] - lds_off[e]) == BM;
     int sid[A_CH + NSL];
 #pragma unroll
     for (int i = 0; i < A_CH; ++i) {
@@ -365,7 +375,11 @@ void moe_gemm_tiled(GroupedGemm g) {
         if (i >= q0 && i < q1) dma16(src.a[i] + (kt * KB & src.am[i]), base + (i * LW + lw) * 1024);
 #pragma unroll
       for (int i = 0; i < B_CH; ++i)
-        if (A_CH + i >= q0 && A_CH + i < q1) dma16(src.b[i] + kt * BB, base + A_BYTES + (i * LW + lw) * 1024);
+        if (A_CH + i >= q0 && A_CH + i < q1) {
+          const uint32_t dst = base + A_BYTES + (i * LW + lw) * 1024;
+          if (src.once) dma16_nt(src.b[i] + kt * BB, dst);
+          else dma16(src.b[i] + kt * BB, dst);
+        }
     }
     if (q1 < N_DMA) return;
 #pragma unroll
