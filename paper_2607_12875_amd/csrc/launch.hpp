@@ -19,6 +19,18 @@ hipError_t launch_router_gate(const uint16_t* hidden, const uint16_t* wr, int T,
                               int renorm, float scale, const float* bias, float* logits_out, int32_t* ids,
                               float* w, int32_t* ids2, float* w2, void* ws, hipStream_t s);
 
+// The router's logits as K-slice partials [KS][T][E] in ws (up to 1024 tokens): returns KS in *ks.
+hipError_t launch_router_partial(const uint16_t* hidden, const uint16_t* wr, int T, int H, int E, void* ws, int* ks,
+                                 hipStream_t s);
+
+// Gate (on logits [T,E] with KS = 0, or on KS router partials) and permute in
+// one launch, where gate_permute_fits.
+bool gate_permute_fits(int T, int E, int k);
+hipError_t launch_gate_permute(const float* lg, int KS, const float* bias, int T, int E, int k, int mode, int renorm,
+                               float scale, float* logits_out, int32_t* ids, float* w, int32_t* ids2, float* w2,
+                               int block_m, int32_t* offsets, int32_t* sorted_ids, int32_t* inv_pos, int cap,
+                               hipStream_t s);
+
 int permute_chunk(int E);
 size_t permute_workspace_bytes(int T, int k, int E);
 hipError_t launch_permute(const int32_t* ids, int T, int k, int E, int block_m, int32_t* offsets,

@@ -267,18 +267,35 @@ moe_status run_layer(const moe_args* a, void* ws, size_t ws_bytes, hipEvent_t* e
   int32_t* inv = at<int32_t>(ws, L.inv_pos);
 
   if (!mark(0)) return MOE_ERR_HIP;
-  const hipError_t gate_err =
-      a->w_router
-          ? moe::launch_router_gate(a->hidden, a->w_router, a->T, a->H, a->E, a->top_k, a->score_mode,
-                                    a->renormalize, a->routed_scale, a->sel_bias, a->logits_out, ids, wts,
-                                    a->topk_ids_out, a->topk_w_out, at<void>(ws, L.router_ws), stream)
-          : moe::launch_gate_topk(a->logits, a->sel_bias, a->T, a->E, a->top_k, a->score_mode, a->renormalize,
-                                  a->routed_scale, ids, wts, a->topk_ids_out, a->topk_w_out, stream);
-  if (gate_err != hipSuccess) return MOE_ERR_HIP;
-  if (!mark(1)) return MOE_ERR_HIP;
-  if (moe::launch_permute(ids, a->T, a->top_k, a->E, L.block_m, offs, sorted, inv, L.cap,
-                          at<void>(ws, L.permute_ws), stream) != hipSuccess)
-    return MOE_ERR_HIP;
+  void* const router_ws = a->w_router ? at<void>(ws, L.router_ws) : nullptr;
+  if (moe::gate_permute_fits(a->T, a->E, a->top_k)) {
+    // a small batch: selection and permute in one launch (the permute stage is empty)
+    const float* lg = a->logits;
+    int KS = 0;
+    if (a->w_router) {
+      if (moe::launch_router_partial(a->hidden, a->w_router, a->T, a->H, a->E, router_ws, &KS, stream) != hipSuccess)
+        return MOE_ERR_HIP;
+      lg = static_cast<const float*>(router_ws);
+    }
+    if (moe::launch_gate_permute(lg, KS, a->sel_bias, a->T, a->E, a->top_k, a->score_mode, a->renormalize,
+                                 a->routed_scale, a->logits_out, ids, wts, a->topk_ids_out, a->topk_w_out, L.block_m,
+                                 offs, sorted, inv, L.cap, stream) != hipSuccess)
+      return MOE_ERR_HIP;
+    if (!mark(1)) return MOE_ERR_HIP;
+  } else {
+    const hipError_t gate_err =
+        a->w_router
+            ? moe::launch_router_gate(a->hidden, a->w_router, a->T, a->H, a->E, a->top_k, a->score_mode,
+                                      a->renormalize, a->routed_scale, a->sel_bias, a->logits_out, ids, wts,
+                                      a->topk_ids_out, a->topk_w_out, router_ws, stream)
+            : moe::launch_gate_topk(a->logits, a->sel_bias, a->T, a->E, a->top_k, a->score_mode, a->renormalize,
+                                    a->routed_scale, ids, wts, a->topk_ids_out, a->topk_w_out, stream);
+    if (gate_err != hipSuccess) return MOE_ERR_HIP;
+    if (!mark(1)) return MOE_ERR_HIP;
+    if (moe::launch_permute(ids, a->T, a->top_k, a->E, L.block_m, offs, sorted, inv, L.cap,
+                            at<void>(ws, L.permute_ws), stream) != hipSuccess)
+      return MOE_ERR_HIP;
+  }
 
   moe::GroupedGemm g;
   g.x = a->hidden;

@@ -309,6 +309,24 @@ size_t router_workspace_bytes(int T, int H, int E) {
   return static_cast<size_t>(router_ks(T, H, E)) * T * E * sizeof(float);
 }
 
+hipError_t launch_router_partial(const uint16_t* hidden, const uint16_t* wr, int T, int H, int E, void* ws, int* ks,
+                                 hipStream_t s) {
+  if (!router_split(T) || router_as_gemm(T, E)) return hipErrorInvalidValue;
+  const int KS = router_ks(T, H, E), hs = H / KS;
+  float* part = static_cast<float*>(ws);
+  if (T > kRouterSplitMaxT) {
+    const dim3 gm((T + 16 * kMidTT - 1) / (16 * kMidTT), (E + 63) / 64, KS);
+    hipLaunchKernelGGL((router_partial_kernel<kMidTT, 4>), gm, dim3(256), 0, s, hidden, wr, T, H, E, hs, part);
+  } else {
+    const dim3 g1((T + 15) / 16, (E + 63) / 64, KS);
+    // all of a short slice's K steps in flight at once
+    if (hs <= 128) hipLaunchKernelGGL((router_partial_kernel<1, 4>), g1, dim3(256), 0, s, hidden, wr, T, H, E, hs, part);
+    else hipLaunchKernelGGL((router_partial_kernel<1, 8>), g1, dim3(256), 0, s, hidden, wr, T, H, E, hs, part);
+  }
+  *ks = KS;
+  return hipGetLastError();
+}
+
 hipError_t launch_router_gate(const uint16_t* hidden, const uint16_t* wr, int T, int H, int E, int k, int mode,
                               int renorm, float scale, const float* bias, float* logits_out, int32_t* ids,
                               float* w, int32_t* ids2, float* w2, void* ws, hipStream_t s) {
@@ -361,17 +379,10 @@ hipError_t launch_router_gate(const uint16_t* hidden, const uint16_t* wr, int T,
 #undef MOE_ROUTER_CASE
     return hipGetLastError();
   }
-  const int KS = router_ks(T, H, E), hs = H / KS;
-  float* part = static_cast<float*>(ws);
-  if (T > kRouterSplitMaxT) {
-    const dim3 gm((T + 16 * kMidTT - 1) / (16 * kMidTT), (E + 63) / 64, KS);
-    hipLaunchKernelGGL((router_partial_kernel<kMidTT, 4>), gm, dim3(256), 0, s, hidden, wr, T, H, E, hs, part);
-  } else {
-    const dim3 g1((T + 15) / 16, (E + 63) / 64, KS);
-    // all of a short slice's K steps in flight at once
-    if (hs <= 128) hipLaunchKernelGGL((router_partial_kernel<1, 4>), g1, dim3(256), 0, s, hidden, wr, T, H, E, hs, part);
-    else hipLaunchKernelGGL((router_partial_kernel<1, 8>), g1, dim3(256), 0, s, hidden, wr, T, H, E, hs, part);
-  }
+  int KS = 0;
+  const hipError_t err = launch_router_partial(hidden, wr, T, H, E, ws, &KS, s);
+  if (err != hipSuccess) return err;
+  const float* part = static_cast<const float*>(ws);
   const dim3 g2((T + 3) / 4);
 #define MOE_ROUTER_SEL(N)                                                                                  \
   hipLaunchKernelGGL(router_select_kernel<N>, g2, dim3(256), 0, s, part, KS, T, E, k, mode, renorm, scale, \

@@ -11,6 +11,23 @@ from tests.gpu_util import check_forward, require_gpu
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("T,E,k", [(1, 1, 1), (1, 256, 32), (16, 64, 32), (16, 65, 6), (16, 256, 8), (17, 256, 8), (16, 257, 8)])
+@pytest.mark.parametrize("masked", [False, True])
+def test_gate_and_permute_of_small_batches(dev, T, E, k, masked):
+    # up to 16 tokens and 256 experts the gate and the permute are one launch:
+    # ids, offsets, sorted ids and inverse positions bit-exact on either side
+    # of its limits (17 tokens, 257 experts), over rank and arg-max selection,
+    # with equal logits and, masked, most experts at -inf
+    cfg = synth.tiny_config(3, T=T, H=128, E=E, I=128, top_k=k)
+    inp = synth.make_inputs(cfg)
+    rng = np.random.default_rng(T + E)
+    lg = rng.integers(-2, 3, size=(T, E)).astype(np.float32)
+    if masked:
+        lg[rng.random((T, E)) < 0.8] = -np.inf
+        lg[:, 0] = 1.0
+    check_forward(cfg, dict(inp, logits=lg))
+
+
 @pytest.fixture(scope="module")
 def dev():
     return require_gpu()
