@@ -295,8 +295,9 @@ moe_status moe_forward(const moe_args* a, void* ws, size_t ws_bytes, hipStream_t
 /*
  * moe_forward with per-stage timing: the same launches on the same stream,
  * with events[i] recorded before stage i and events[MOE_NUM_STAGES] after the
- * last stage.  Stages: 0 gate, 1 permute, 2 fp8 activation quantisation
- * (empty for bf16 / int4), 3 GEMM1 + SiLU*up, 4 GEMM2, 5 combine.
+ * last stage.  Stages: 0 gate, 1 permute (empty up to 16 tokens and 256
+ * experts, where the gate's launch does it), 2 fp8 activation quantisation or
+ * int4 group sums (empty for bf16), 3 GEMM1 + SiLU*up, 4 GEMM2, 5 combine.
  *   events  host array of MOE_NUM_STAGES + 1 caller-created hipEvent_t; a
  *           NULL entry skips that mark (e.g. only GEMM1 bracketed: entries 3
  *           and 4 set)
@@ -314,7 +315,8 @@ moe_status moe_forward_profiled(const moe_args* a, void* ws, size_t ws_bytes,
  * MOE_STATIC_WS_BYTES, one per GPU, which exists from the first use of the
  * library on that GPU until the process ends.  The caller still passes
  * every input and output in `a`.  The call allocates nothing.
- *   a       as moe_forward; moe_workspace_bytes(a) must not exceed
+ *   a       as moe_forward; moe_workspace_bytes(a), less the int4 group sums
+ *           of the intermediate (which have their own room), must not exceed
  *           MOE_STATIC_WS_BYTES, else MOE_ERR_WORKSPACE (nothing enqueued).
  * Every call on one GPU shares that GPU's array and leaves its intermediates
  * there (nothing in it needs to start zeroed): calls that overlap on one GPU

@@ -519,15 +519,15 @@ void moe_gemm_tiled(GroupedGemm g) {
                        : wn * WTN + (j) * 32)
 
     // Row blocks (of 32) of the tile that hold routed rows: the last tile of an
-    // expert is padded, on average by half a tile, and the split bf16 and
-    // MXFP4 loops below, which the matrix pipe's time bounds, leave the blocks
-    // of pads out (every wave holds all BM rows, so all gain alike).  Layer
+    // expert is padded, on average by half a tile, and the split loops below
+    // leave the blocks of pads out (every wave holds all BM rows, so all gain alike).  Layer
     // before and after: bf16, 4096 x 1408 x 64 experts, top 6, 4096 tokens 1198
     // and 1181 us, 777 tokens 506 and 498; MXFP4, 7168 x 2048 x 256 experts,
-    // top 8, 8192 tokens 6392 and 6180 us.  The fp8 and MXFP8 products, bound
-    // by their copies, keep 2 x 2 waves.
+    // top 8, 8192 tokens 6392 and 6180 us; fp8, the same layer, 8192 tokens 4169
+    // and 4106 us, 2000 tokens 1894 and 1819, 300 tokens 1235 and 1161.  The
+    // MXFP8 products, bound by their copies, keep 2 x 2 waves.
     constexpr bool I4P = FMT == 2 && KB == 512;  // int4 on the software-pipelined loop
-    constexpr bool SKIP = NP > 0 && (FMT == 0 || FMT == 4 || I4P);
+    constexpr bool SKIP = NP > 0 && (FMT == 0 || FMT == 1 || FMT == 4 || I4P);
     static_assert(!SKIP || (WM == 1 && (TM == 4 || TM == 2)), "every wave holds all row blocks");
     int nb = TM;
     if constexpr (SKIP) nb = __popcll(__ballot(lane < TM && g.sorted_ids[m0 + 32 * (lane % TM)] < g.n_routed));
@@ -583,6 +583,83 @@ void moe_gemm_tiled(GroupedGemm g) {
               for (int j = 0; j < TN; ++j)
                 acc[i][j] = TRB ? mfma32x32x16(fb[kk & 1][j], fa[kk & 1][i], acc[i][j])
                                 : mfma32x32x16(fa[kk & 1][i], fb[kk & 1][j], acc[i][j]);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+      });
+    }
+    if constexpr (NP > 0 && FMT == 1) {
+      // fp8 math waves of a split launch (two waves per SIMD, so at most 256
+      // registers each): transposed product as below, but one 32x32 block
+      // at a time -- its two K halves are MFMAs on one partial, and the
+      // VALU folds the previous block's partial in between them -- with
+      // the A fragments read per row block, one block ahead.
+      for_blocks([&](auto nbc) {
+        constexpr int NB = decltype(nbc)::value;
+        for (int kt = 0; kt < nk; ++kt) {
+          bar();  // every stage-kt copy of every copy wave has landed
+          const uint8_t* As = &smem[(sb + kt) % STAGES][0];
+          const uint8_t* Bs = As + A_BYTES;
+          const uint8_t* Ss = Bs + B_BYTES;
+          auto read8 = [&](const uint8_t* row, int r, int kk) {  // K half kk of a row: this lane's 32 bytes
+            const int c0 = 4 * kk + 2 * kg;
+            const i32x4 lo = __builtin_bit_cast(i32x4, ld16(row + ((c0 ^ swz<KB>(r)) << 4)));
+            const i32x4 hi = __builtin_bit_cast(i32x4, ld16(row + (((c0 + 1) ^ swz<KB>(r)) << 4)));
+            return i32x8(__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+          };
+          i32x8 bq[TN][2];
+#pragma unroll
+          for (int j = 0; j < TN; ++j) {
+            const int r = brow(j) + l32;
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk) bq[j][kk] = read8(Bs + r * BB, r, kk);
+          }
+          i32x8 af[2][2];  // [buffer][K half] of one row block
+          auto read_a = [&](int i, int buf) {
+            const int r = wm * WTM + i * 32 + l32;
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk) af[buf][kk] = read8(As + r * KB, r, kk);
+          };
+          read_a(0, 0);
+          const float* sA = reinterpret_cast<const float*>(Ss);                    // [BM]
+          const float* sB = reinterpret_cast<const float*>(Ss + (BM / 64) * 256);  // [64]
+          float fa[NB], sw[TN];
+#pragma unroll
+          for (int i = 0; i < NB; ++i) fa[i] = sA[wm * WTM + i * 32 + l32];
+#pragma unroll
+          for (int j = 0; j < TN; ++j) {
+            const int r = brow(j);
+            sw[j] = GEMM1 ? sB[r < NC ? 0 : 1] : sB[(r / 128) % (BNW / 128)];
+          }
+          f32x16 part[2];
+          // blocks row-major: b = i*TN + j
+#pragma unroll
+          for (int b = 0; b <= NB * TN; ++b) {
+            const int i = b / TN, j = b % TN;
+            const int ip = (b - 1) / TN, jp = (b - 1) % TN;  // the block folded in this iteration
+            if (b < NB * TN && j == 0 && i + 1 < NB) read_a(i + 1, (i + 1) & 1);
+            __builtin_amdgcn_sched_barrier(0);
+            const float f = b > 0 ? fa[ip] * sw[jp] : 0.f;
+            if (b < NB * TN) part[b & 1] = mfma32x32x64_fp8(bq[j][0], af[i & 1][0], f32x16{});
+            if (b > 0) {
+#pragma unroll
+              for (int v = 0; v < 8; ++v) acc[ip][jp][v] = fmaf(part[(b - 1) & 1][v], f, acc[ip][jp][v]);
+            }
+            if (b < NB * TN) part[b & 1] = mfma32x32x64_fp8(bq[j][1], af[i & 1][1], part[b & 1]);
+            if (b > 0) {
+#pragma unroll
+              for (int v = 8; v < 16; ++v) acc[ip][jp][v] = fmaf(part[(b - 1) & 1][v], f, acc[ip][jp][v]);
+            }
+            // keep the order written: each MFMA, then eight fmas that run on the
+            // VALU while it executes (the compiler otherwise pairs the MFMAs and
+            // stalls the fmas behind the second one)
+            if (b > 0 && b < NB * TN) {
+              __builtin_amdgcn_sched_group_barrier(0x002, 1, 0);  // the scale product
+              __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+              __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
+              __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+              __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
+            }
             __builtin_amdgcn_sched_barrier(0);
           }
         }
@@ -867,77 +944,6 @@ void moe_gemm_tiled(GroupedGemm g) {
           if (pre) issue_part(cur, kt + STAGES - 1, (sb + kt + STAGES - 1) % STAGES, kk * PER, min((kk + 1) * PER, A_CH + B_CH));
           __builtin_amdgcn_sched_barrier(0);
         }
-      } else if constexpr (FMT == 1 && NP > 0) {
-        // fp8 math waves of a split launch (two waves per SIMD, so at most 256
-        // registers each): transposed product as below, but one 32x32 block
-        // at a time -- its two K halves are MFMAs on one partial, and the
-        // VALU folds the previous block's partial in between them -- with
-        // the W fragments read per column block, one block ahead.
-        i32x8 af[2][TM];
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk) {
-          const int c0 = 4 * kk + 2 * kg;
-#pragma unroll
-          for (int i = 0; i < TM; ++i) {
-            const int r = wm * WTM + i * 32 + l32;
-            const i32x4 lo = __builtin_bit_cast(i32x4, ld16(As + r * KB + ((c0 ^ swz<KB>(r)) << 4)));
-            const i32x4 hi = __builtin_bit_cast(i32x4, ld16(As + r * KB + (((c0 + 1) ^ swz<KB>(r)) << 4)));
-            af[kk][i] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-          }
-        }
-        i32x8 bq[2][2];  // [buffer][K half] of one column block
-        auto read_b = [&](int j, int buf) {
-          const int r = brow(j) + l32;
-#pragma unroll
-          for (int kk = 0; kk < 2; ++kk) {
-            const int c0 = 4 * kk + 2 * kg;
-            const i32x4 lo = __builtin_bit_cast(i32x4, ld16(Bs + r * BB + ((c0 ^ swz<KB>(r)) << 4)));
-            const i32x4 hi = __builtin_bit_cast(i32x4, ld16(Bs + r * BB + (((c0 + 1) ^ swz<KB>(r)) << 4)));
-            bq[buf][kk] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-          }
-        };
-        read_b(0, 0);
-        const float* sA = reinterpret_cast<const float*>(Ss);                    // [BM]
-        const float* sB = reinterpret_cast<const float*>(Ss + (BM / 64) * 256);  // [64]
-        float fa[TM], sb[TN];
-#pragma unroll
-        for (int i = 0; i < TM; ++i) fa[i] = sA[wm * WTM + i * 32 + l32];
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const int r = brow(j);
-          sb[j] = GEMM1 ? sB[r < NC ? 0 : 1] : sB[(r / 128) % (BNW / 128)];
-        }
-        f32x16 part[2];
-        // blocks column-major: b = j*TM + i
-#pragma unroll
-        for (int b = 0; b <= TM * TN; ++b) {
-          const int i = b % TM, j = b / TM;
-          const int ip = (b - 1) % TM, jp = (b - 1) / TM;  // the block folded in this iteration
-          if (b < TM * TN && i == 0 && j + 1 < TN) read_b(j + 1, (j + 1) & 1);
-          __builtin_amdgcn_sched_barrier(0);
-          const float f = b > 0 ? fa[ip] * sb[jp] : 0.f;
-          if (b < TM * TN) part[b & 1] = mfma32x32x64_fp8(bq[j & 1][0], af[0][i], f32x16{});
-          if (b > 0) {
-#pragma unroll
-            for (int v = 0; v < 8; ++v) acc[ip][jp][v] = fmaf(part[(b - 1) & 1][v], f, acc[ip][jp][v]);
-          }
-          if (b < TM * TN) part[b & 1] = mfma32x32x64_fp8(bq[j & 1][1], af[1][i], part[b & 1]);
-          if (b > 0) {
-#pragma unroll
-            for (int v = 8; v < 16; ++v) acc[ip][jp][v] = fmaf(part[(b - 1) & 1][v], f, acc[ip][jp][v]);
-          }
-          // keep the order written: each MFMA, then eight fmas that run on the
-          // VALU while it executes (the compiler otherwise pairs the MFMAs and
-          // stalls the fmas behind the second one)
-          if (b > 0 && b < TM * TN) {
-            __builtin_amdgcn_sched_group_barrier(0x002, 1, 0);  // the scale product
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
-          }
-          __builtin_amdgcn_sched_barrier(0);
-        }
       } else if constexpr (FMT == 1) {
         // Transposed product: the MFMA's first operand is a 32-row block of
         // W (output columns n), the second a 32-row block of A (rows m), so
@@ -1164,6 +1170,7 @@ void moe_gemm_tiled(GroupedGemm g) {
         // the other k-group lane, then the WN waves (LDS).
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
+          if (i >= nb) break;  // blocks of pads are never read
           float m = 0.f;
 #pragma unroll
           for (int j = 0; j < TH; ++j)
@@ -1176,6 +1183,7 @@ void moe_gemm_tiled(GroupedGemm g) {
         uint8_t* q = static_cast<uint8_t*>(g.inter);
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
+          if (i >= nb) break;
           const int rl = wm * WTM + i * 32 + l32;
           float m = 0.f;
 #pragma unroll
@@ -1418,7 +1426,7 @@ hipError_t launch_gemm2_bf16_tiled(const GroupedGemm& g, hipStream_t s) {
 }
 
 // fp8 over the 128 x 256 tile: with copy waves (NP > 0) four math waves
-// (2 x 2), else eight (MOE_F8_WM x MOE_F8_WN) that copy for themselves
+// (1 x 4), else eight (MOE_F8_WM x MOE_F8_WN) that copy for themselves
 #ifndef MOE_F8_WM
 #define MOE_F8_WM 2
 #define MOE_F8_WN 4
@@ -1432,7 +1440,7 @@ hipError_t launch_gemm2_bf16_tiled(const GroupedGemm& g, hipStream_t s) {
 int gemm_block_m_fp8(int, int, int) { return 128; }
 template <bool GEMM1, int BNW, int NP>
 hipError_t launch_fp8(const GroupedGemm& g, hipStream_t s) {
-  if constexpr (NP > 0) return launch_tiled<1, GEMM1, 128, BNW, 2, 2, MOE_TGM, 128, 3, NP>(g, s);
+  if constexpr (NP > 0) return launch_tiled<1, GEMM1, 128, BNW, 1, 4, MOE_TGM, 128, 3, NP>(g, s);
   else return launch_tiled<1, GEMM1, 128, BNW, MOE_F8_WM, MOE_F8_WN, MOE_TGM>(g, s);
 }
 hipError_t launch_gemm1_fp8(const GroupedGemm& g, hipStream_t s) {
