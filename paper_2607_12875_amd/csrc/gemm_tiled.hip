@@ -524,10 +524,9 @@ void moe_gemm_tiled(GroupedGemm g) {
     // before and after: bf16, 4096 x 1408 x 64 experts, top 6, 4096 tokens 1198
     // and 1181 us, 777 tokens 506 and 498; MXFP4, 7168 x 2048 x 256 experts,
     // top 8, 8192 tokens 6392 and 6180 us; fp8, the same layer, 8192 tokens 4169
-    // and 4106 us, 2000 tokens 1894 and 1819, 300 tokens 1235 and 1161.  The
-    // MXFP8 products, bound by their copies, keep 2 x 2 waves.
+    // and 4106 us, 2000 tokens 1894 and 1819, 300 tokens 1235 and 1161.
     constexpr bool I4P = FMT == 2 && KB == 512;  // int4 on the software-pipelined loop
-    constexpr bool SKIP = NP > 0 && (FMT == 0 || FMT == 1 || FMT == 4 || I4P);
+    constexpr bool SKIP = NP > 0 && (FMT == 0 || FMT == 1 || FMT == 4 || MX8 || I4P);
     static_assert(!SKIP || (WM == 1 && (TM == 4 || TM == 2)), "every wave holds all row blocks");
     int nb = TM;
     if constexpr (SKIP) nb = __popcll(__ballot(lane < TM && g.sorted_ids[m0 + 32 * (lane % TM)] < g.n_routed));
@@ -768,6 +767,92 @@ void moe_gemm_tiled(GroupedGemm g) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
               }
             }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        };
+        for (int kt = 0; kt + 1 < nk; ++kt) step(kt, std::false_type{});
+        step(nk - 1, std::true_type{});
+      });
+    }
+    if constexpr (NP > 0 && MX8) {
+      // Math waves of an MXFP4 x MXFP8 launch, formed transposed like fp8
+      // (the weight fragment is the first operand).  MFMA kk of the step
+      // covers K [64 kk, 64 kk + 64) in two 32-element scale blocks, and lane
+      // group kg supplies block kg's E8M0 byte for both operands (byte
+      // 2 (kk % 2) + kg of the row's dword kk / 2 for the step; the
+      // instruction applies the scales itself, so the products accumulate
+      // in place: no rescale on the VALU).  Weights: lane group kg holds
+      // block kg, 16 bytes (chunk 2 kk + kg of the row's KE/2 bytes).
+      // Activations: the e4m3 operand interleaves the blocks in 16-element
+      // halves -- lane group kg holds elements [16 kg, +16) of block 0,
+      // then of block 1, i.e. chunks 4 kk + kg and 4 kk + 2 + kg of the
+      // row's KE bytes.  Fragments are read one substep ahead; chunk addresses
+      // are one XOR on the stage's (rows aligned to their bytes).  With the row
+      // blocks of pads left out, 7168 x 2048 x 256 experts, top 8: 8192 tokens
+      // 3693 and 3664 us, 2000 tokens 1453 and 1411, 64 tokens 675 and 653.
+      for_blocks([&](auto nbc) {
+        constexpr int NB = decltype(nbc)::value;
+        constexpr int NKK = 2 * MXD;
+        static_assert(STAGE % 256 == 0 && A_BYTES % 256 == 0, "rows aligned to their bytes");
+        i32x8 fa[2][NB];
+        i32x4 fb[2][TN];
+        int da[2][NB], db[2][TN];  // the rows' scale dwords
+        const int ra = l32, rb = brow(0) + l32;
+        const uint32_t oa = ra * KB + ((kg ^ swz<KB>(ra)) << 4);
+        const uint32_t ob = A_BYTES + rb * BB + ((kg ^ swz_b<BB>(rb)) << 4);
+        typedef const __attribute__((address_space(3))) int* lds_i32;
+        auto read_frags = [&](int kt, int kk, int buf) {
+          const uint32_t st = smem0 + ((sb + kt) % STAGES) * STAGE;
+          const uint32_t pa = st + oa, pb = st + ob;
+          const uint32_t sa = st + A_BYTES + B_BYTES + (kk / 2) * BM * 4 + ra * 4;                  // [MXD][BM]
+          const uint32_t sw = st + A_BYTES + B_BYTES + MXD * BM * 4 + (kk / 2) * BNW * 4 + rb * 4;  // [MXD][BNW]
+#pragma unroll
+          for (int i = 0; i < NB; ++i) {
+            const i32x4 lo = __builtin_bit_cast(i32x4, lds16((pa ^ (4 * kk) << 4) + i * 32 * KB));
+            const i32x4 hi = __builtin_bit_cast(i32x4, lds16((pa ^ (4 * kk + 2) << 4) + i * 32 * KB));
+            fa[buf][i] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+            da[buf][i] = *(lds_i32)(sa + i * 32 * 4);
+          }
+#pragma unroll
+          for (int j = 0; j < TN; ++j) {
+            fb[buf][j] = __builtin_bit_cast(i32x4, lds16((pb ^ (2 * kk) << 4) + (brow(j) - brow(0)) * BB));
+            db[buf][j] = *(lds_i32)(sw + (brow(j) - brow(0)) * 4);
+          }
+        };
+        bar();  // stage 0 has landed
+        read_frags(0, 0, 0);
+        auto step = [&](int kt, auto last) {  // the last step apart, as above
+#pragma unroll
+          for (int kk = 0; kk < NKK; ++kk) {
+            if (kk + 1 < NKK) {
+              read_frags(kt, kk + 1, (kk + 1) & 1);
+            } else if (!decltype(last)::value) {
+              __atomic_signal_fence(__ATOMIC_SEQ_CST);
+              lds_wait();  // stage kt is in registers
+              bar();       // stage kt+1 has landed; buffer kt is free
+              read_frags(kt + 1, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            int sw[TN];
+#pragma unroll
+            for (int j = 0; j < TN; ++j) sw[j] = static_cast<int>(static_cast<uint32_t>(db[kk & 1][j]) >> (8 * kg));
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+              const int sa = static_cast<int>(static_cast<uint32_t>(da[kk & 1][i]) >> (8 * kg));
+#pragma unroll
+              for (int j = 0; j < TN; ++j) {
+                const i32x4 q = fb[kk & 1][j];
+                const i32x8 w = __builtin_shufflevector(q, q, 0, 1, 2, 3, 0, 1, 2, 3);  // upper half unused
+                acc[i][j] = (kk & 1) ? mfma32x32x64_f4f8<2>(w, fa[kk & 1][i], sw[j], sa, acc[i][j])
+                                     : mfma32x32x64_f4f8<0>(w, fa[kk & 1][i], sw[j], sa, acc[i][j]);
+              }
+            }
+            // the products stay in their substep: without a use here they were
+            // moved past the later substeps' reads, whose fragments then spilled
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+              for (int j = 0; j < TN; ++j) asm volatile("" : "+v"(acc[i][j]));
             __builtin_amdgcn_sched_barrier(0);
           }
         };
@@ -1086,57 +1171,6 @@ void moe_gemm_tiled(GroupedGemm g) {
             for (int j = 0; j < TN; ++j) acc[i][j] = mfma32x32x16(a[kk & 1][i], b[j], acc[i][j]);
           __builtin_amdgcn_sched_barrier(0);
         }
-      } else if constexpr (MX8) {
-        // MXFP4 weights x MXFP8 activations, formed transposed like fp8 (the
-        // weight fragment is the first operand).  MFMA kk of the step covers
-        // K [64 kk, 64 kk + 64) in two 32-element scale blocks, and lane
-        // group kg supplies block kg's E8M0 byte for both operands (byte
-        // 2 (kk % 2) + kg of the row's dword kk / 2 for the step; the
-        // instruction applies the scales itself, so the products accumulate
-        // in place: no rescale on the VALU).  Weights: lane group kg holds
-        // block kg, 16 bytes (chunk 2 kk + kg of the row's KE/2 bytes).
-        // Activations: the e4m3 operand interleaves the blocks in 16-element
-        // halves -- lane group kg holds elements [16 kg, +16) of block 0,
-        // then of block 1, i.e. chunks 4 kk + kg and 4 kk + 2 + kg of the
-        // row's KE bytes.
-        const uint32_t* sA = reinterpret_cast<const uint32_t*>(Ss);                          // [MXD][BM]
-        const uint32_t* sB = reinterpret_cast<const uint32_t*>(Ss + MXD * (BM / 64) * 256);  // [MXD][BNW]
-        // per 128 K elements (one E8M0 dword per row): MFMAs 2 d and 2 d + 1
-#pragma unroll
-        for (int d = 0; d < MXD; ++d) {
-          i32x8 af[2][TM], bq[2][TN];
-#pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            const int kk = 2 * d + h;
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-              const int r = wm * WTM + i * 32 + l32;
-              const i32x4 lo = __builtin_bit_cast(i32x4, ld16(As + r * KB + (((4 * kk + kg) ^ swz<KB>(r)) << 4)));
-              const i32x4 hi = __builtin_bit_cast(i32x4, ld16(As + r * KB + (((4 * kk + 2 + kg) ^ swz<KB>(r)) << 4)));
-              af[h][i] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-            }
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-              const int r = brow(j) + l32;
-              const i32x4 q = __builtin_bit_cast(i32x4, ld16(Bs + r * BB + (((2 * kk + kg) ^ swz_b<BB>(r)) << 4)));
-              bq[h][j] = __builtin_shufflevector(q, q, 0, 1, 2, 3, 0, 1, 2, 3);  // upper half unused
-            }
-          }
-          int da[TM], db[TN];  // the row's dword d moved down by kg bytes: byte 2 h is block 2 h + kg
-#pragma unroll
-          for (int i = 0; i < TM; ++i) da[i] = static_cast<int>(sA[d * BM + wm * WTM + i * 32 + l32] >> (8 * kg));
-#pragma unroll
-          for (int j = 0; j < TN; ++j) db[j] = static_cast<int>(sB[d * BNW + brow(j) + l32] >> (8 * kg));
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) acc[i][j] = mfma32x32x64_f4f8<0>(bq[0][j], af[0][i], db[j], da[i], acc[i][j]);
-#pragma unroll
-          for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) acc[i][j] = mfma32x32x64_f4f8<2>(bq[1][j], af[1][i], db[j], da[i], acc[i][j]);
-        }
       }
     }
 #undef brow
@@ -1220,6 +1254,7 @@ void moe_gemm_tiled(GroupedGemm g) {
         uint8_t* q = static_cast<uint8_t*>(g.inter);
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
+          if (i >= nb) break;  // blocks of pads are never read
           const size_t row = static_cast<size_t>(m0 + wm * WTM + i * 32 + l32);
 #pragma unroll
           for (int j = 0; j < TH; ++j) {
@@ -1501,8 +1536,8 @@ hipError_t launch_gemm2_mxfp4_tiled(const GroupedGemm& g, hipStream_t s) {
 template <bool GEMM1, int BNW>
 hipError_t launch_mx8(const GroupedGemm& g, hipStream_t s) {
   const int K = GEMM1 ? g.H : g.I;
-  if (K % 256 == 0) return launch_tiled<5, GEMM1, 128, BNW, 2, 2, MOE_TGM, 256, 2, 4>(g, s);
-  return launch_tiled<5, GEMM1, 128, BNW, 2, 2, MOE_TGM, 128, 4, 4>(g, s);
+  if (K % 256 == 0) return launch_tiled<5, GEMM1, 128, BNW, 1, 4, MOE_TGM, 256, 2, 4>(g, s);
+  return launch_tiled<5, GEMM1, 128, BNW, 1, 4, MOE_TGM, 128, 4, 4>(g, s);
 }
 hipError_t launch_gemm1_mx8(const GroupedGemm& g, hipStream_t s) { return launch_mx8<true, 256>(g, s); }
 hipError_t launch_gemm2_mx8(const GroupedGemm& g, hipStream_t s) {

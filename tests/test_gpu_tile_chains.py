@@ -31,9 +31,10 @@ def test_mxfp8_four_stage_chained_tiles(dev):
     check_forward(synth.tiny_config(9, T=600, H=4096, E=16, I=1152, top_k=4))
 
 
-@pytest.mark.parametrize("n,H,I", [(3, 512, 136), (8, 512, 256), (8, 384, 128)])
+@pytest.mark.parametrize("n,H,I", [(3, 512, 136), (8, 512, 256), (8, 384, 128), (4, 512, 256), (4, 384, 128),
+                                   (9, 512, 256), (9, 384, 128)])
 def test_padded_row_blocks(dev, n, H, I):
-    # bf16 (ragged K and columns too) and MXFP4 tiles with one to four live
+    # bf16 (ragged K and columns too), MXFP4, fp8 and MXFP4 x MXFP8 tiles with one to four live
     # 32-row blocks, on either side of each boundary: every token picks expert
     # e with probability falling in e, so segment lengths spread over the tile;
     # the routed rows are counted to be sure
