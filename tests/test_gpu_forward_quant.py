@@ -241,6 +241,8 @@ def test_int4_zero_and_wide_scales(dev):
 
 @pytest.mark.parametrize("T,H,I", [(70, 512, 128),     # K of the second product one step
                                    (33, 640, 384),     # 128-column tiles of the second product
+                                   (45, 640, 256),     # the same with one 256-element step
+                                   (90, 256, 512),     # one 256-element step in the first product
                                    (300, 1280, 1152)])  # tiles whose second row block is all pads, and full ones
 def test_int4_tiled_second_product(dev, T, H, I):
     # The oracle rounds the intermediate to bf16 where the layer does; codes
