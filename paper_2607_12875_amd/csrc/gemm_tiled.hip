@@ -189,6 +189,7 @@ void moe_gemm_tiled(GroupedGemm g) {
   };
 
   constexpr int NSL = SC > 0 ? SC : 1;
+  constexpr bool ONCE = FMT != 4 && !(FMT == 2 && KB == 256);  // non-temporal copies of weights read once (see sources)
   struct Src {
     const uint8_t* a[A_CH];  // A rows
     int am[A_CH];            // A step-advance mask: -1, or 0 for a pad row (its source is the zero chunk)
@@ -217,8 +218,10 @@ void moe_gemm_tiled(GroupedGemm g) {
     // layer 1257 us without, 1218 with; bf16, 777 tokens 493 and 477; int4, 512
     // tokens 365 and 359).  With two or more row tiles the hint costs the
     // sharing (prefill GEMM1 675 -> 973 us with it everywhere).  The 128-element
-    // int4 steps, whose registers are all taken, stay without.
-    constexpr bool ONCE = !(FMT == 2 && KB == 256);
+    // int4 steps, whose registers are all taken, stay without, and so does
+    // MXFP4, where the choice cost the copy waves more (8192 tokens 6243 us
+    // without, 6332 with).  The choice is made once per step: one per copy
+    // cost the bf16 layer of 4096 tokens 7 %.
     src.once = ONCE && __builtin_amdgcn_readfirstlane(lds_off[e + 1] - lds_off[e]) == BM;
     int sid[A_CH + NSL];
 #pragma unroll
@@ -373,13 +376,15 @@ void moe_gemm_tiled(GroupedGemm g) {
 #pragma unroll
       for (int i = 0; i < A_CH; ++i)
         if (i >= q0 && i < q1) dma16(src.a[i] + (kt * KB & src.am[i]), base + (i * LW + lw) * 1024);
+      if (ONCE && src.once) {
 #pragma unroll
-      for (int i = 0; i < B_CH; ++i)
-        if (A_CH + i >= q0 && A_CH + i < q1) {
-          const uint32_t dst = base + A_BYTES + (i * LW + lw) * 1024;
-          if (src.once) dma16_nt(src.b[i] + kt * BB, dst);
-          else dma16(src.b[i] + kt * BB, dst);
-        }
+        for (int i = 0; i < B_CH; ++i)
+          if (A_CH + i >= q0 && A_CH + i < q1) dma16_nt(src.b[i] + kt * BB, base + A_BYTES + (i * LW + lw) * 1024);
+      } else {
+#pragma unroll
+        for (int i = 0; i < B_CH; ++i)
+          if (A_CH + i >= q0 && A_CH + i < q1) dma16(src.b[i] + kt * BB, base + A_BYTES + (i * LW + lw) * 1024);
+      }
     }
     if (q1 < N_DMA) return;
 #pragma unroll
