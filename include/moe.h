@@ -89,7 +89,10 @@ typedef enum {
      their running sums divided by the current group's scale, so a ratio r
      between groups multiplies them by r, and 2^64 keeps them inside the fp32
      range with about 2^30 to spare for the sums themselves (the decode sizes
-     scale each group's own partial and have no such limit).
+     scale each group's own partial and have no such limit).  Outputs of the
+     second product that this form does not hold (an intermediate value of
+     Inf, a group whose sum times 136 overflows, scales beyond those above)
+     are sums of a * (q * scale) instead (slower).
      Scales from a per-group amax quantiser of real weight rows differ by a
      few powers of two. */
   MOE_W_INT4_G128 = 2,

@@ -69,6 +69,25 @@ __device__ __forceinline__ bf16x8 int4x8_biased_bf16(uint32_t w, uint32_t mask) 
   return as_bf16x8(u32x4{dw(w), dw(w >> 4), dw(w >> 8), dw(w >> 12)});
 }
 
+// One output of the int4 second product, sum over k of a[k] * (q[k] * s[k / 128])
+// in fp32, for the values that the tile's biased form cannot hold (below): `a`
+// an intermediate row in the codes' order, `w` and `s` a weight row's codes and
+// group scales.
+__device__ float int4_dot(const uint16_t* a, const uint32_t* w, const uint16_t* s, int K) {
+  float sum = 0.f;
+  for (int k8 = 0; k8 < K / 8 && sum == sum; ++k8) {
+    const float sc = bf16_to_f32(s[k8 / 16]);
+    const uint32_t word = w[k8];
+    const u32x4 x = ld16(a + 8 * k8);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {  // element j: half j / 4 of dword j % 4
+      const float q = static_cast<float>(static_cast<int>(word << (28 - 4 * j)) >> 28);
+      sum = fmaf(__uint_as_float(j < 4 ? x[j % 4] << 16 : x[j % 4] & 0xFFFF0000u), q * sc, sum);
+    }
+  }
+  return sum;
+}
+
 // XOR swizzle of the 16-byte chunks of a 128-byte LDS row: row r stores its
 // chunk c in slot c ^ swz<KB>(r).  For the fragment reads (32 consecutive rows,
 // lanes l and l+32 on neighbouring chunks of one row) (r >> 1) & 7 measured
@@ -518,6 +537,7 @@ void moe_gemm_tiled(GroupedGemm g) {
     float seff[TN];  // int4: the scale each column's accumulators are divided by (0: none yet)
 #pragma unroll
     for (int j = 0; j < TN; ++j) seff[j] = 0.f;
+    float least = 1.f;  // int4 GEMM2: the smallest ratio of this lane's columns' scales, group to group
 
     // B row (within the tile) of wave tile j
 #define brow(j) (GEMM1 ? ((j) < TN / 2 ? wn * (WTN / 2) + (j) * 32 : NC + wn * (WTN / 2) + ((j) - TN / 2) * 32) \
@@ -924,6 +944,7 @@ void moe_gemm_tiled(GroupedGemm g) {
             const bool z = sc == 0.f;
             const float se = z ? seff[j] : sc;
             ratio[j] = seff[j] == 0.f ? 0.f : seff[j] * __builtin_amdgcn_rcpf(se);
+            if (!GEMM1) least = fminf(least, seff[j] == 0.f ? 1.f : fabsf(ratio[j]));
             seff[j] = se;
             keep[j] = z ? 0u : 0x000F000Fu;
           }
@@ -1124,6 +1145,7 @@ void moe_gemm_tiled(GroupedGemm g) {
           const bool z = sc == 0.f;
           const float se = z ? seff[j] : sc;
           ratio[j] = seff[j] == 0.f ? 0.f : seff[j] * __builtin_amdgcn_rcpf(se);  // 1-ulp reciprocal
+          if (!GEMM1) least = fminf(least, seff[j] == 0.f ? 1.f : fabsf(ratio[j]));
           seff[j] = se;
           keep[j] = z ? 0u : 0x000F000Fu;
         }
@@ -1333,6 +1355,7 @@ void moe_gemm_tiled(GroupedGemm g) {
     } else if constexpr (FMT == 2) {
       // direct layout, fp32 y: the tile's routed rows come before its pads
       const int live = __popcll(__ballot(live_row)) - 4 * kg;
+      float top = 0.f;  // largest magnitude of this lane's outputs
       static_assert(FMT != 2 || BM == 64, "one row per lane in the ballot");
 #pragma unroll
       for (int i = 0; i < TM; ++i)
@@ -1342,8 +1365,35 @@ void moe_gemm_tiled(GroupedGemm g) {
           if (r >= live) continue;  // pad rows are never read
           float* yr = static_cast<float*>(g.y) + static_cast<size_t>(m0 + r + 4 * kg) * g.H + n0 + wn * WTN + l32;
 #pragma unroll
-          for (int j = 0; j < TN; ++j) yr[j * 32] = acc[i][j][v];
+          for (int j = 0; j < TN; ++j) {
+            yr[j * 32] = acc[i][j][v];
+            top = __builtin_elementwise_maximum(top, fabsf(acc[i][j][v]));  // NaN if one is
+          }
         }
+      // An intermediate value of Inf, a group whose sum times 136 passes the
+      // fp32 range, or scales that fall too far (subnormal ones included: their
+      // reciprocal overflows): the biased form gives NaN or Inf, as
+      // Inf * (136 + q) - 136 * Inf, where the sum itself may have a value.
+      // Scales that rise too far leave nothing of the groups before.  Those
+      // outputs are formed again from the codes themselves, one lane each:
+      // slow, and nothing to any other tile (half an instruction per output
+      // and one per scale; 4000 tokens, 7168 x 2048 x 256 experts, top 8:
+      // 3706 us without the checks, 3709 with; the range of every ratio
+      // compared on both sides took 3787).
+      const bool wide = least < 0x1p-64f;
+      if (__builtin_expect(wide || !(top < INFINITY), 0)) {
+        for (int b = 0; b < TM * 16 * TN; ++b) {
+          const int r = wm * WTM + (b / TN / 16) * 32 + 8 * (b / TN % 16 >> 2) + (b / TN & 3);
+          if (r >= live) continue;
+          const size_t row = static_cast<size_t>(m0 + r + 4 * kg);
+          const int n = n0 + wn * WTN + b % TN * 32 + l32;
+          float* y = static_cast<float*>(g.y) + row * g.H + n;
+          if (!wide && fabsf(*y) < INFINITY) continue;
+          const size_t wr = static_cast<size_t>(e) * g.H + n;
+          *y = int4_dot(static_cast<const uint16_t*>(g.inter) + row * g.I, static_cast<const uint32_t*>(g.w2) + wr * (g.I / 8),
+                        static_cast<const uint16_t*>(g.w2_scale) + wr * (g.I / 128), g.I);
+        }
+      }
     } else {
       // transposed layout, fp32 y: four consecutive output columns per 16-byte store
       static_assert(TRB && y_is_f32(FMT), "bf16-activation routes keep y in fp32");

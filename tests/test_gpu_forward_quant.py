@@ -258,6 +258,58 @@ def test_int4_tiled_second_product(dev, T, H, I):
     assert rel <= 2.0 ** -11, rel
 
 
+def _int4_words(q):
+    u = (q & 15).to(torch.int64).view(*q.shape[:-1], -1, 8)
+    v = sum(u[..., j] << (4 * j) for j in range(8))
+    return torch.where(v >= 2 ** 31, v - 2 ** 32, v).int().contiguous()
+
+
+@pytest.mark.parametrize("T,H,I", [(80, 256, 256), (80, 384, 512), (200, 256, 384), (80, 128, 1152)])
+@pytest.mark.parametrize("column,s2", [(None, (-7, -7)),      # nothing out of the ordinary
+                                       (62, (-7, -7)),        # a column of the intermediate reaches Inf
+                                       (58, (-100, -7)),      # and values whose sum times 136 would, or do
+                                       (None, (-60, 60)), (None, (60, -60)), (None, (-7, -130)), (None, (-130, -7)),
+                                       (None, (-130, -128)), (None, (-120, 120)), (None, (120, -120)),
+                                       ("zero", (-100, 60))])  # all of the sum in the first group
+def test_int4_second_product_outside_the_biased_range(dev, T, H, I, column, s2):
+    # Values and scales (powers of two: of the first group, of the others) that
+    # the codes' biased form 136 + q cannot hold: the outputs are those of
+    # sum a * (q * s).  Per output the error is at most 2^-8 of sum |a q s|
+    # for intermediate values tipped to the other bf16 neighbour, plus, of the
+    # biased sums, I * 143 * 2^-24 <= 2^-6.6 of it (at |q| >= 1).
+    E = 4
+    gen = torch.Generator(device="cuda").manual_seed(T + H + I)
+    hid = torch.randn(T, H, device="cuda", generator=gen).bfloat16()
+    lg = torch.randn(T, E, device="cuda", generator=gen)
+
+    def codes(*shape):
+        q = torch.randint(1, 8, shape, device="cuda", generator=gen)
+        return q * (1 - 2 * torch.randint(0, 2, shape, device="cuda", generator=gen))
+
+    q1, q2 = codes(E, 2 * I, H), codes(E, H, I)
+    s1 = torch.full((E, 2 * I, H // 128), 0.01, device="cuda").bfloat16()
+    if column == "zero":
+        s1[:, 128:I] = 0
+    elif column is not None:
+        s1[:, 5] = s1[:, I + 5] = 2.0 ** column
+        q2[:, ::3, 5] = 0  # 0 * Inf
+    f2 = torch.full((E, H, I // 128), 2.0 ** s2[1], dtype=torch.float64, device="cuda")
+    f2[:, :, 0] = 2.0 ** s2[0]
+    out, _ = moe.moe_forward(hid, lg, _int4_words(q1), _int4_words(q2), 1, wfmt="int4", w1_scale=s1,
+                             w2_scale=f2.bfloat16())
+    e = lg.argmax(1)
+    g = torch.stack([(q1[e[t]].double() * s1[e[t]].double().repeat_interleave(128, 1)) @ hid[t].double() for t in range(T)])
+    a = (torch.nn.functional.silu(g[:, :I]) * g[:, I:]).float().bfloat16().double()
+    w = q2.double() * f2.repeat_interleave(128, 2)
+    p = a[:, None, :] * w[e]
+    ref, size = p.sum(2).float(), p.abs().sum(2)
+    assert bool(ref.isinf().any()) == (column in (62, 58))
+    fin = ref.isfinite()
+    assert torch.equal(out.isnan(), ref.isnan())
+    assert torch.equal(out[~fin & ~ref.isnan()], ref[~fin & ~ref.isnan()])
+    assert bool(((out - ref)[fin].abs() <= (2.0 ** -8 + 2.0 ** -24 * 143 * I) * size[fin]).all())
+
+
 # ---- int4 decode route: the 16-row streamed kernels up to 8 routed rows per
 # expert on average; both products sum each 128-group of codes exactly and
 # apply the row's group scale to the group's partial in fp32
