@@ -262,8 +262,7 @@ typedef struct moe_ws_layout {
   int64_t inter, inter_s;            /* bf16 [cap,I] (fp8: uint8 [cap,I], fp32 [cap,I/128];
                                         MXFP8: uint8 [cap,I], uint8 [cap,I/32] E8M0;
                                         int4 above the decode sizes: every eight
-                                        columns in the order {0,4,1,5,2,6,3,7},
-                                        their group sums at the workspace's end) */
+                                        columns in the order {0,4,1,5,2,6,3,7}) */
   int64_t y;                         /* [cap,H] rows in sorted order: bf16 for
                                         MOE_W_FP8E4M3_B128 and MOE_W_MXFP4_MXFP8,
                                         fp32 otherwise; pad rows unspecified */
@@ -318,8 +317,7 @@ moe_status moe_forward_profiled(const moe_args* a, void* ws, size_t ws_bytes,
  * MOE_STATIC_WS_BYTES, one per GPU, which exists from the first use of the
  * library on that GPU until the process ends.  The caller still passes
  * every input and output in `a`.  The call allocates nothing.
- *   a       as moe_forward; moe_workspace_bytes(a), less the int4 group sums
- *           of the intermediate (which have their own room), must not exceed
+ *   a       as moe_forward; moe_workspace_bytes(a) must not exceed
  *           MOE_STATIC_WS_BYTES, else MOE_ERR_WORKSPACE (nothing enqueued).
  * Every call on one GPU shares that GPU's array and leaves its intermediates
  * there (nothing in it needs to start zeroed): calls that overlap on one GPU

@@ -211,40 +211,76 @@ hipError_t launch_act_quant_mx(const uint16_t* x, int M, int K, uint8_t* q, uint
   return hipGetLastError();
 }
 
-// Per (row, 128-column group): -136 times the fp32 sum of the group's values,
-// the term the int4 products take off their biased codes (136 + q).  Sixteen
-// lanes (one DPP row) own one group, as in the quantiser above.  With xp the
-// eight columns of each thread also go out in the order the codes decode to
-// (dword d: columns d and d + 4).  With rows, only that many rows are live.
-__global__ __launch_bounds__(256) void group_sum_kernel(const uint16_t* __restrict__ x, int M, int K,
-                                                         float* __restrict__ out, uint16_t* __restrict__ xp,
-                                                         const int32_t* __restrict__ rows) {
-  const long idx = static_cast<long>(blockIdx.x) * 256 + threadIdx.x;  // one per 8 columns
-  const long total = static_cast<long>(rows ? min(*rows, M) : M) * (K / 8);
-  const bool live = idx < total;
-  uint4 v = make_uint4(0, 0, 0, 0);
-  if (live) v = *reinterpret_cast<const uint4*>(x + idx * 8);
-  const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+// -136 times the fp32 sum of a 128-column group, the term the int4 products take
+// off their biased codes (136 + q), on the sixteen lanes (one DPP row) that own
+// the group, eight columns v each, as in the quantiser above.
+__device__ __forceinline__ float biased_group_sum(const uint4& v) {
+  const uint16_t* h = reinterpret_cast<const uint16_t*>(&v);
   float sum = 0.f;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) sum += __uint_as_float(u[i] << 16) + __uint_as_float(u[i] & 0xFFFF0000u);
+  for (int i = 0; i < 8; ++i) sum += bf16_to_f32(h[i]);
   sum += dpp_f32<0xB1>(sum);
   sum += dpp_f32<0x4E>(sum);
   sum += dpp_f32<0x141>(sum);
   sum += dpp_f32<0x140>(sum);
-  if (!live) return;
-  if ((threadIdx.x & 15) == 0) out[idx / 16] = -136.0f * sum;
-  if (xp)
-    *reinterpret_cast<uint4*>(xp + idx * 8) =
-        make_uint4(__builtin_amdgcn_perm(v.z, v.x, 0x05040100u), __builtin_amdgcn_perm(v.z, v.x, 0x07060302u),
-                   __builtin_amdgcn_perm(v.w, v.y, 0x05040100u), __builtin_amdgcn_perm(v.w, v.y, 0x07060302u));
+  return -136.0f * sum;
 }
 
-hipError_t launch_group_sum(const uint16_t* x, int M, int K, float* out, uint16_t* xp, const int32_t* rows,
-                            hipStream_t st) {
+// The hidden rows' sums [M][K/128], and the rows in the order the codes decode
+// to (dword d of eight columns: columns d and d + 4).
+__global__ __launch_bounds__(256) void group_sum_kernel(const uint16_t* __restrict__ x, int M, int K,
+                                                         float* __restrict__ out, uint16_t* __restrict__ xp) {
+  const long idx = static_cast<long>(blockIdx.x) * 256 + threadIdx.x;  // one per 8 columns
+  const bool live = idx < static_cast<long>(M) * (K / 8);
+  uint4 v = make_uint4(0, 0, 0, 0);
+  if (live) v = *reinterpret_cast<const uint4*>(x + idx * 8);
+  const float sum = biased_group_sum(v);
+  if (!live) return;
+  if ((threadIdx.x & 15) == 0) out[idx / 16] = sum;
+  *reinterpret_cast<uint4*>(xp + idx * 8) =
+      make_uint4(__builtin_amdgcn_perm(v.z, v.x, 0x05040100u), __builtin_amdgcn_perm(v.z, v.x, 0x07060302u),
+                 __builtin_amdgcn_perm(v.w, v.y, 0x05040100u), __builtin_amdgcn_perm(v.w, v.y, 0x07060302u));
+}
+
+hipError_t launch_group_sum(const uint16_t* x, int M, int K, float* out, uint16_t* xp, hipStream_t st) {
   const long total = static_cast<long>(M) * (K / 8);
   const dim3 grid(static_cast<unsigned>((total + 255) / 256)), block(256);
-  hipLaunchKernelGGL(group_sum_kernel, grid, block, 0, st, x, M, K, out, xp, rows);
+  hipLaunchKernelGGL(group_sum_kernel, grid, block, 0, st, x, M, K, out, xp);
+  return hipGetLastError();
+}
+
+// The intermediate's sums, for the second product: workgroup (64-row tile,
+// group) writes the 64 rows' sums once per column tile of width `cols`, into
+// that tile's own part of y (64 rows of ld floats), as 64 consecutive floats at
+// 64 * group of the part read row by row.  So a step of the product reads
+// whole lines (two per group; 64, a line per row, with the sums at the start
+// of each row of y: 512 tokens, 4096 x 1536 x 128 experts, top 8, 373 us,
+// 362 this way), and a tile alone reads what it will overwrite.
+__global__ __launch_bounds__(256) void tile_sum_kernel(const uint16_t* __restrict__ x, int K, float* __restrict__ y,
+                                                        int ld, int cols, const int32_t* __restrict__ rows) {
+  __shared__ float sums[64];
+  const int m0 = blockIdx.x * 64, grp = blockIdx.y;
+  if (m0 >= *rows) return;  // uniform
+  const int r0 = threadIdx.x >> 4;
+  const uint16_t* p = x + static_cast<size_t>(m0 + r0) * K + grp * 128 + (threadIdx.x & 15) * 8;
+  uint4 v[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = *reinterpret_cast<const uint4*>(p + static_cast<size_t>(16 * i) * K);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float s = biased_group_sum(v[i]);
+    if ((threadIdx.x & 15) == 0) sums[16 * i + r0] = s;
+  }
+  __syncthreads();
+  const int at = 64 * grp;
+  float* o = y + static_cast<size_t>(m0 + at / cols) * ld + at % cols + lane_id();
+  for (int n0 = (threadIdx.x >> 6) * cols; n0 < ld; n0 += 4 * cols) o[n0] = sums[lane_id()];
+}
+
+hipError_t launch_tile_sums(const uint16_t* x, int max_rows, int K, float* y, int ld, int cols, const int32_t* rows,
+                            hipStream_t st) {
+  if (max_rows < 64) return hipSuccess;
+  hipLaunchKernelGGL(tile_sum_kernel, dim3(max_rows / 64, K / 128), dim3(256), 0, st, x, K, y, ld, cols, rows);
   return hipGetLastError();
 }
 

@@ -106,7 +106,9 @@ __device__ __forceinline__ int swz_b(int r) { return BB == 32 ? (r >> 2) & 1 : B
 // waves never touch global memory in the main loop, so a stalled load queue
 // (L1 waiting on L2) cannot hold up the MFMA stream behind an in-order copy
 // instruction.  NP == 0: the math waves issue the copies themselves.
-template <int FMT, bool GEMM1, int BM, int BNW, int WM, int WN, int GM, int KBT = 128, int STAGES = 3, int NP = 0>
+// SUMS (int4): the rows' group sums are there; else the bias comes off by MFMAs.
+template <int FMT, bool GEMM1, int BM, int BNW, int WM, int WN, int GM, int KBT = 128, int STAGES = 3, int NP = 0,
+          bool SUMS = true>
 // The 64-row 4-bit GEMMs with copy waves are held to 128 registers, which keeps two workgroups per CU.
 __global__ __launch_bounds__((WM * WN + NP) * 64) __attribute__((amdgpu_waves_per_eu((FMT == 2 || FMT == 4) && (GEMM1 || NP > 0) && BM == 64 && KBT < 512 ? 4 : 1)))
 void moe_gemm_tiled(GroupedGemm g) {
@@ -142,12 +144,13 @@ void moe_gemm_tiled(GroupedGemm g) {
   // each (64 floats); fp8: slots [0, BM/64) the row scales of A, slot BM/64
   // the block scales of B; int4: slots [0, BNW/64) the bf16 pair holding each
   // B row's group scale and slots [BNW/64, BNW/64 + BM/64) the
-  // rows' biased group sums (x_gsum).  Copy wave lw fills slots lw, lw + LW, ...
+  // rows' biased group sums (GEMM1: x_gsum; GEMM2: in y).  Copy wave lw fills slots lw, lw + LW, ...
   // MXFP8: MXD E8M0 dwords per row per step (four 32-element blocks each);
   // slots [0, MXD BM/64) the A rows' dwords (slot d BM/64 + g: dword d of
   // row group g), then MXD BNW/64 slots of the B rows' likewise; slots past
   // those load a harmless dummy.
   constexpr bool GSUM = FMT == 2;
+  static_assert(SUMS || (GSUM && KBT < 512), "group sums are int4's; the 256-element steps need them");
   constexpr int GD = GSUM ? KE / 128 : 1;  // int4: scale groups per step
   constexpr int MXD = MX8 ? KE / 128 : 1;
   constexpr int NSLOT = FMT == 0 ? 0 : (MX8 ? MXD * (BM + BNW) / 64 : (GSUM ? 2 : 1) * NW);
@@ -333,12 +336,14 @@ void moe_gemm_tiled(GroupedGemm g) {
           src.s[k] = reinterpret_cast<const uint8_t*>(static_cast<const uint16_t*>(GEMM1 ? g.w1_scale : g.w2_scale) +
                                                       (static_cast<size_t>(e) * (GEMM1 ? 2 * g.I : g.H) + n) * (K / 128));
           src.ss[k] = 1;  // advanced per step in elements below
-        } else if (GSUM && sl < BNW / 64 + GD * BM / 64) {
+        } else if (SUMS && sl < BNW / 64 + GD * BM / 64) {
           // tile row (sl - BNW/64) % (BM/64) * 64 + lane: its sum over the
-          // step's group (sl - BNW/64) / (BM/64), GD floats per step
+          // step's group (sl - BNW/64) / (BM/64); GEMM1 GD floats per step,
+          // GEMM2 (64 rows, one slot per group) as launch_tile_sums lays them out
+          static_assert(!SUMS || BM == 64, "one slot per group");
           const int d = (sl - BNW / 64) / (BM / 64), r = (sl - BNW / 64) % (BM / 64) * 64 + lane;
           if (GEMM1) src.s[k] = reinterpret_cast<const uint8_t*>(g.x_gsum + token(sid[A_CH + k]) * (g.H / 128) + d);
-          else src.s[k] = reinterpret_cast<const uint8_t*>(g.inter_gsum + static_cast<size_t>(m0 + r) * (g.I / 128) + d);
+          else src.s[k] = reinterpret_cast<const uint8_t*>(static_cast<const float*>(g.y) + static_cast<size_t>(m0) * g.H + n0 + 64 * d + lane);
           src.ss[k] = 4 * GD;
         }
       } else if constexpr (MX8) {
@@ -417,11 +422,14 @@ void moe_gemm_tiled(GroupedGemm g) {
       } else if constexpr (FMT == 2) {
         // B scale words (ss 1): element kt*KE/128 of the row, rounded down to
         // an even element (4-byte aligned); group sums advance one float per
-        // group (ss 4 GD); dummies stay put (ss 0)
+        // group (ss 4 GD) or as they lie in y; dummies stay put (ss 0)
         const uint8_t* p = src.s[k] + kt * src.ss[k];
         if (src.ss[k] == 1) {
           const uintptr_t a = reinterpret_cast<uintptr_t>(src.s[k]) + ((kt * KE) / 128) * 2;
           p = reinterpret_cast<const uint8_t*>(a & ~static_cast<uintptr_t>(3));
+        } else if (SUMS && !GEMM1) {
+          const int at = 64 * GD * kt;
+          p = src.s[k] + (static_cast<size_t>(at / BNW) * g.H + at % BNW) * 4;
         }
         dma4(p, dst);
       }
@@ -1152,9 +1160,9 @@ void moe_gemm_tiled(GroupedGemm g) {
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
           const int r0 = wm * WTM + i * 32 + 4 * kg;  // value v: row r0 + 8*(v/4) + v%4
-          f32x16 rs;
+          f32x16 rs{};
 #pragma unroll
-          for (int b4 = 0; b4 < 4; ++b4) {
+          for (int b4 = 0; b4 < (SUMS ? 4 : 0); ++b4) {
             const u32x4 q = ld16(sR + r0 + 8 * b4);
 #pragma unroll
             for (int c = 0; c < 4; ++c) rs[4 * b4 + c] = __uint_as_float(q[c]);
@@ -1196,6 +1204,13 @@ void moe_gemm_tiled(GroupedGemm g) {
           for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j) acc[i][j] = mfma32x32x16(a[kk & 1][i], b[j], acc[i][j]);
+          if constexpr (!SUMS) {
+            const bf16x8 off = as_bf16x8(u32x4{0xC308C308u, 0xC308C308u, 0xC308C308u, 0xC308C308u});  // -136
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+              for (int j = 0; j < TN; ++j) acc[i][j] = mfma32x32x16(a[kk & 1][i], off, acc[i][j]);
+          }
           __builtin_amdgcn_sched_barrier(0);
         }
       }
@@ -1445,7 +1460,8 @@ dim3 persistent_grid(int per_cu, long max_tiles) {
   return dim3(static_cast<unsigned>(std::max<long>(kXcds, std::min(n, cap))));
 }
 
-template <int FMT, bool GEMM1, int BM, int BNW, int WM, int WN, int GM, int KBT = 128, int STAGES = 3, int NP = 0>
+template <int FMT, bool GEMM1, int BM, int BNW, int WM, int WN, int GM, int KBT = 128, int STAGES = 3, int NP = 0,
+          bool SUMS = true>
 hipError_t launch_tiled(const GroupedGemm& g, hipStream_t s) {
   constexpr int NC = GEMM1 ? BNW / 2 : BNW;
   constexpr int NT = (WM * WN + NP) * 64;
@@ -1454,7 +1470,7 @@ hipError_t launch_tiled(const GroupedGemm& g, hipStream_t s) {
   constexpr int KE = (FMT == 1 || FMT == 5) ? KBT : KBT / 2;
   if (FMT != 0 && (GEMM1 ? g.H : g.I) % KE != 0) return hipErrorInvalidValue;
   const long mt = g.max_rows / BM, nt = ((GEMM1 ? g.I : g.H) + NC - 1) / NC;
-  auto kern = moe_gemm_tiled<FMT, GEMM1, BM, BNW, WM, WN, GM, KBT, STAGES, NP>;
+  auto kern = moe_gemm_tiled<FMT, GEMM1, BM, BNW, WM, WN, GM, KBT, STAGES, NP, SUMS>;
   // workgroups per CU depend on the kernel's registers and LDS only: queried
   // once per instantiation (thread-safe static initialisation)
   static const int per_cu = occupancy_per_cu(kern, NT);
@@ -1554,10 +1570,21 @@ hipError_t launch_gemm2_fp8(const GroupedGemm& g, hipStream_t s) {
 #define MOE_TI4_STAGES 2
 #endif
 int gemm_block_m_int4(int, int, int) { return MOE_TI4_BM; }
+// Where GEMM2 finds the intermediate's group sums: each of its tiles, BNW
+// columns wide, reads them from its own part of y (64 rows, room for BNW groups
+// of 64 sums), which it overwrites when it has read them all.  An intermediate of
+// more groups goes without (the bias comes off by MFMAs of its own, which doubles
+// them): returns 0.
+int int4_sum_columns(int H, int I) {
+  const int bnw = H % 256 ? 128 : 256;
+  return I / 128 <= bnw ? bnw : 0;
+}
 // 256 K elements per step (whole weight lines, one workgroup per CU) where K
 // is a multiple of that, else 128
 template <bool GEMM1, int BNW>
 hipError_t launch_int4(const GroupedGemm& g, hipStream_t s) {
+  if constexpr (!GEMM1)
+    if (!g.inter_sums) return launch_tiled<2, false, MOE_TI4_BM, BNW, 1, 4, MOE_TGM_INT4, MOE_TI4_KB, MOE_TI4_STAGES, MOE_TI4_NP2, false>(g, s);
   if ((GEMM1 ? g.H : g.I) % 256 == 0) return launch_tiled<2, GEMM1, MOE_TI4_BM, BNW, 1, 4, MOE_TGM_INT4, 512, 2, 4>(g, s);
   return launch_tiled<2, GEMM1, MOE_TI4_BM, BNW, 1, 4, MOE_TGM_INT4, MOE_TI4_KB, MOE_TI4_STAGES, GEMM1 ? MOE_TI4_NP1 : MOE_TI4_NP2>(g, s);
 }

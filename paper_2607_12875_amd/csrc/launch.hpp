@@ -45,11 +45,17 @@ hipError_t launch_act_quant(const uint16_t* x, int M, int K, uint8_t* q, float* 
 // OCP MX e4m3 per (row, 32 columns): codes q [M,K] and E8M0 bytes sx [M,K/32]
 hipError_t launch_act_quant_mx(const uint16_t* x, int M, int K, uint8_t* q, uint8_t* sx, hipStream_t st);
 // out[m][g] = -136 * sum of x[m][128g, 128g + 128) in fp32 (the int4 products'
-// bias term).  xp, if given, receives x with every eight columns in the order
-// {0,4,1,5,2,6,3,7} (the order the int4 codes decode to); rows, if given, is
-// the device count of rows to do (at most M).
-hipError_t launch_group_sum(const uint16_t* x, int M, int K, float* out, uint16_t* xp, const int32_t* rows,
+// bias term).  xp receives x with every eight columns in the order
+// {0,4,1,5,2,6,3,7} (the order the int4 codes decode to).
+hipError_t launch_group_sum(const uint16_t* x, int M, int K, float* out, uint16_t* xp, hipStream_t st);
+// The same sums of 64-row tiles of x, once per column tile (64 rows by `cols`
+// columns) of y [max_rows][ld]: the tile's rows' sums over group g are floats
+// [64 g, 64 g + 64) of that part of y, row by row (K/128 <= cols).  rows: the
+// device count of rows, a multiple of 64 of at most max_rows.
+hipError_t launch_tile_sums(const uint16_t* x, int max_rows, int K, float* y, int ld, int cols, const int32_t* rows,
                             hipStream_t st);
+// Width of the int4 GEMM2's column tiles, where each finds its rows' group sums in y, or 0.
+int int4_sum_columns(int H, int I);
 
 // Grouped expert GEMMs.  Rows are the permuted routed rows (sorted order),
 // grouped by expert in segments padded to a multiple of the kernel's row tile;
@@ -69,7 +75,7 @@ struct GroupedGemm {
   const void* w2_scale;
   void* inter;                // [cap, I] bf16 (fp8, MXFP8: e4m3 codes)
   float* inter_scale;         // fp8 only: [cap, I/128]
-  const float* inter_gsum;    // tiled int4 only: [cap, I/128], -136 * the sum of each 128-group of an intermediate row
+  bool inter_sums;            // tiled int4 only: y holds the intermediate's group sums (launch_tile_sums)
   uint8_t* inter_mx;          // MXFP8 only: E8M0 bytes [cap, I/32]
   void* y;                    // [cap, H]: fp32 for bf16 weights, bf16 otherwise
 };

@@ -69,13 +69,6 @@ moe_status check_args(const moe_args* a) {
   return MOE_OK;
 }
 
-// Tiled int4: the intermediate rows' group sums (one fp32 per 128 columns, 1/64
-// of the intermediate's own bytes).
-size_t int4_gsum_bytes(const moe_args* a, long cap) {
-  if (a->wfmt != MOE_W_INT4_G128 || moe::int4_decode(a->T, a->top_k, a->E, a->H, a->I)) return 0;
-  return align_up(static_cast<size_t>(cap) * (a->I / 128) * 4);
-}
-
 // Workspace layout for validated sizes (T may be 0).
 moe_ws_layout make_layout(const moe_args* a) {
   moe_ws_layout L;
@@ -114,7 +107,6 @@ moe_ws_layout make_layout(const moe_args* a) {
   L.y = take(static_cast<size_t>(cap) * a->H * (moe::y_is_f32(a->wfmt) ? 4 : 2));
   L.permute_ws = take(moe::permute_workspace_bytes(a->T, a->top_k, a->E));
   L.router_ws = a->w_router ? take(moe::router_workspace_bytes(a->T, a->H, a->E)) : -1;
-  take(int4_gsum_bytes(a, cap));  // at the layout's end
   L.total = static_cast<int64_t>(off);
   return L;
 }
@@ -302,14 +294,14 @@ moe_status run_layer(const moe_args* a, void* ws, size_t ws_bytes, hipEvent_t* e
   g.x_scale = nullptr;
   g.x_mx = nullptr;
   g.x_gsum = nullptr;
-  g.inter_gsum = nullptr;
+  g.inter_sums = false;
   if (!mark(2)) return MOE_ERR_HIP;
   if (a->wfmt == MOE_W_INT4_G128 && !moe::int4_decode(a->T, a->top_k, a->E, a->H, a->I)) {
     // the reordered hidden rows (T*H bf16) lie in y's region (cap >= T rows of
     // H fp32), which is written only after GEMM1 has read them
     float* gs = at<float>(ws, L.act_s);
     uint16_t* xp = at<uint16_t>(ws, L.y);
-    if (moe::launch_group_sum(a->hidden, a->T, a->H, gs, xp, nullptr, stream) != hipSuccess) return MOE_ERR_HIP;
+    if (moe::launch_group_sum(a->hidden, a->T, a->H, gs, xp, stream) != hipSuccess) return MOE_ERR_HIP;
     g.x = xp;
     g.x_gsum = gs;
   }
@@ -347,12 +339,11 @@ moe_status run_layer(const moe_args* a, void* ws, size_t ws_bytes, hipEvent_t* e
   if (!mark(3)) return MOE_ERR_HIP;
   if (moe::launch_gemm1(a->wfmt, g, stream) != hipSuccess) return MOE_ERR_HIP;
   if (!mark(4)) return MOE_ERR_HIP;
-  if (g.x_gsum) {  // tiled int4
-    float* gs = at<float>(ws, L.total - static_cast<int64_t>(int4_gsum_bytes(a, L.cap)));
-    if (moe::launch_group_sum(static_cast<const uint16_t*>(g.inter), L.cap, a->I, gs, nullptr, offs + a->E, stream) !=
-        hipSuccess)
+  if (const int cols = g.x_gsum ? moe::int4_sum_columns(a->H, a->I) : 0; cols > 0) {  // tiled int4
+    if (moe::launch_tile_sums(static_cast<const uint16_t*>(g.inter), L.cap, a->I, at<float>(ws, L.y), a->H, cols,
+                              offs + a->E, stream) != hipSuccess)
       return MOE_ERR_HIP;
-    g.inter_gsum = gs;
+    g.inter_sums = true;
   }
   if (moe::launch_gemm2(a->wfmt, g, stream) != hipSuccess) return MOE_ERR_HIP;
   if (!mark(5)) return MOE_ERR_HIP;
@@ -370,11 +361,7 @@ moe_status run_layer(const moe_args* a, void* ws, size_t ws_bytes, hipEvent_t* e
 // process ends.  In host code `scratch` names a host-side stand-in, never the
 // device memory: its device address is looked up once per device and only
 // that address is used.
-// MOE_STATIC_WS_BYTES limits a layer's workspace without the int4 group sums at
-// its end; these are at most 1/64 of it (the intermediate's share) and have
-// their own room.
-constexpr size_t kStaticWsBytes = MOE_STATIC_WS_BYTES + MOE_STATIC_WS_BYTES / 64 + 256;
-static __device__ __align__(256) uint8_t scratch[kStaticWsBytes];
+static __device__ __align__(256) uint8_t scratch[MOE_STATIC_WS_BYTES];
 
 namespace {
 
@@ -411,11 +398,10 @@ moe_status moe_forward_static_ws(const moe_args* a, hipStream_t stream) {
   moe_status st = check_args(a);
   if (st != MOE_OK) return st;
   if (a->T == 0) return MOE_OK;
-  const moe_ws_layout L = make_layout(a);
-  if (static_cast<size_t>(L.total) - int4_gsum_bytes(a, L.cap) > MOE_STATIC_WS_BYTES) return MOE_ERR_WORKSPACE;
+  if (static_cast<size_t>(make_layout(a).total) > MOE_STATIC_WS_BYTES) return MOE_ERR_WORKSPACE;
   void* ws = scratch_on_current_device();
   if (!ws) return MOE_ERR_HIP;
-  return run_layer(a, ws, kStaticWsBytes, nullptr, stream);
+  return run_layer(a, ws, MOE_STATIC_WS_BYTES, nullptr, stream);
 }
 
 moe_status moe_forward_profiled(const moe_args* a, void* ws, size_t ws_bytes,

@@ -245,3 +245,13 @@ def test_bf16_shapes_multiple_of_8_accepted():
     a.logits = None
     a.w_router = FAKE
     assert _fwd(a) == B.MOE_ERR_UNSUPPORTED
+
+
+@pytest.mark.parametrize("T,H,E,I,k", [(300, 256, 8, 128, 2), (512, 4096, 128, 1536, 8), (70, 640, 6, 384, 2)])
+def test_int4_workspace_ends_with_the_layout(T, H, E, I, k):
+    # nothing lies behind the regions that the layout names: a workspace of a
+    # stored size stays large enough, and the static limit is the whole of it
+    a = moe.make_args(T, H, E, I, k, wfmt="int4")
+    L = moe.moe_workspace_layout(a)
+    end = L["permute_ws"] + moe.moe_permute_workspace_bytes(T, k, E)
+    assert L["total"] == moe.moe_workspace_bytes(a) == -(-end // 256) * 256

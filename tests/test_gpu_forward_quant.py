@@ -258,6 +258,19 @@ def test_int4_tiled_second_product(dev, T, H, I):
     assert rel <= 2.0 ** -11, rel
 
 
+@pytest.mark.parametrize("H,I", [(128, 16384), (128, 16512), (256, 32768), (256, 32896)])
+def test_int4_group_sums_of_wide_intermediates(dev, H, I):
+    # as many groups as a column tile of the second product has columns, and
+    # one more, where the product takes the bias off by itself: the bound of
+    # the test above, the fp32 sums over these K adding under 2^-14 of the result
+    cfg = synth.tiny_config(5, T=40, H=H, I=I, E=2, top_k=1)
+    inp = _scale_blocks(synth.make_inputs(cfg), cfg.wfmt, seed=I)
+    out, ref, L = check_forward(cfg, inp)
+    assert L["block_m"] == 64
+    rel = np.linalg.norm(out - ref["out"]) / np.linalg.norm(ref["out"])
+    assert rel <= 2.0 ** -11, rel
+
+
 def _int4_words(q):
     u = (q & 15).to(torch.int64).view(*q.shape[:-1], -1, 8)
     v = sum(u[..., j] << (4 * j) for j in range(8))
