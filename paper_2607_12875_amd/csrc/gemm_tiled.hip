@@ -1574,18 +1574,31 @@ int gemm_block_m_int4(int, int, int) { return MOE_TI4_BM; }
 // columns wide, reads them from its own part of y (64 rows, room for BNW groups
 // of 64 sums), which it overwrites when it has read them all.  An intermediate of
 // more groups goes without (the bias comes off by MFMAs of its own, which doubles
-// them): returns 0.
+// them): returns 0.  So does one of one or two groups, where the launch that
+// sums costs more (8 experts, top 2, H = 256, I = 128: 17 tokens 28.6 us with,
+// 26.5 without, 8192 tokens 55.9 and 53.9; at I = 512, 10000 rows, 66.3 and 67.9).
 int int4_sum_columns(int H, int I) {
   const int bnw = H % 256 ? 128 : 256;
-  return I / 128 <= bnw ? bnw : 0;
+  return I > 256 && I / 128 <= bnw ? bnw : 0;
 }
-// 256 K elements per step (whole weight lines, one workgroup per CU) where K
-// is a multiple of that, else 128
+// 256 K elements per step (whole weight lines) leave room for one workgroup per
+// CU, 128 for two, which hide each other's first steps and epilogues.  256 where
+// K is a multiple of that and long (1536: 512 tokens, 128 experts 359 us, 388
+// with 128), or each workgroup has one tile at most (H = I = 512, 32 experts, top
+// 4, 150 tokens: 33.8 and 36.8 us).  Short K with many tiles takes 128 (8192
+// tokens of that layer 147 and 136 us; H = I = 1024, 8 experts, top 2, 196 and 183).
+template <bool GEMM1, int BNW>
+bool int4_long_steps(const GroupedGemm& g) {
+  const int K = GEMM1 ? g.H : g.I, N = GEMM1 ? g.I : g.H;
+  constexpr int NC = GEMM1 ? BNW / 2 : BNW;
+  const long tiles = static_cast<long>(g.max_rows / MOE_TI4_BM) * ((N + NC - 1) / NC);
+  return K % 256 == 0 && (K >= 1536 || tiles <= cu_count());
+}
 template <bool GEMM1, int BNW>
 hipError_t launch_int4(const GroupedGemm& g, hipStream_t s) {
   if constexpr (!GEMM1)
     if (!g.inter_sums) return launch_tiled<2, false, MOE_TI4_BM, BNW, 1, 4, MOE_TGM_INT4, MOE_TI4_KB, MOE_TI4_STAGES, MOE_TI4_NP2, false>(g, s);
-  if ((GEMM1 ? g.H : g.I) % 256 == 0) return launch_tiled<2, GEMM1, MOE_TI4_BM, BNW, 1, 4, MOE_TGM_INT4, 512, 2, 4>(g, s);
+  if (int4_long_steps<GEMM1, BNW>(g)) return launch_tiled<2, GEMM1, MOE_TI4_BM, BNW, 1, 4, MOE_TGM_INT4, 512, 2, 4>(g, s);
   return launch_tiled<2, GEMM1, MOE_TI4_BM, BNW, 1, 4, MOE_TGM_INT4, MOE_TI4_KB, MOE_TI4_STAGES, GEMM1 ? MOE_TI4_NP1 : MOE_TI4_NP2>(g, s);
 }
 hipError_t launch_gemm1_int4(const GroupedGemm& g, hipStream_t s) { return launch_int4<true, 256>(g, s); }

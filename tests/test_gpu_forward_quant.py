@@ -271,6 +271,17 @@ def test_int4_group_sums_of_wide_intermediates(dev, H, I):
     assert rel <= 2.0 ** -11, rel
 
 
+@pytest.mark.parametrize("T,H,I", [(2100, 1024, 512),   # both products more tiles than CUs: 128-element steps
+                                   (2100, 640, 512),    # 128-column tiles of the second product
+                                   (1000, 1024, 512)])  # fewer: 256-element steps
+def test_int4_steps_of_short_k(dev, T, H, I):
+    cfg = synth.tiny_config(5, T=T, H=H, I=I, E=4, top_k=2)
+    inp = _scale_blocks(synth.make_inputs(cfg), cfg.wfmt, seed=T)
+    out, ref, L = check_forward(cfg, inp)
+    rel = np.linalg.norm(out - ref["out"]) / np.linalg.norm(ref["out"])
+    assert rel <= 2.0 ** -11, rel  # as in the test of the second product above
+
+
 def _int4_words(q):
     u = (q & 15).to(torch.int64).view(*q.shape[:-1], -1, 8)
     v = sum(u[..., j] << (4 * j) for j in range(8))
