@@ -72,13 +72,16 @@ __global__ __launch_bounds__(kPermThreads) void permute_scatter_kernel(
       // every chunk's count of expert tid, up to 64 loads in flight at a time
       // (one round of memory latency up to 64 chunks, i.e. 65536 routed rows;
       // indices clamped so the loads issue unconditionally), 8 where that is
-      // all there are
+      // all there are.  The scheduler is kept from adding between the loads:
+      // it had waited for each of the first sixteen (32768 routed rows, 64
+      // experts, H = I = 256: the layer 80.6 us so, 76.8 now)
       auto sum = [&](auto width) {
         constexpr int W = decltype(width)::value;
         for (int c0 = 0; c0 < nchunks; c0 += W) {
           int v[W];
 #pragma unroll
           for (int u = 0; u < W; ++u) v[u] = counts[min(c0 + u, nchunks - 1) * E + tid];
+          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int u = 0; u < W; ++u) {
             const int cc = c0 + u;
