@@ -57,6 +57,43 @@ def test_gate_integer_ties(dev):
     _check_gate(dev, np.zeros((5, 256), np.float32), np.zeros(256, np.float32), 8, "sigmoid", True, 2.5)
 
 
+@pytest.mark.parametrize("E,k", [(65, 32), (100, 7), (256, 8), (257, 8), (1024, 32)])
+def test_gate_ties_across_lanes(dev, E, k):
+    # several lanes hold the largest key in every round: all equal, all but a
+    # few at -inf, and two values spread over the lanes
+    rng = np.random.default_rng(E)
+    lg = np.zeros((96, E), np.float32)
+    lg[32:64] = -np.inf
+    lg[32:64, rng.integers(0, E, 3)] = 1.0
+    lg[64:] = rng.integers(0, 2, (32, E))
+    _check_gate(dev, lg, None, k)
+
+
+def test_gate_time_does_not_depend_on_ties(dev):
+    # a token whose logits are equal (padding, masked experts) takes about as
+    # long as any other: 17.1 us against 15.0 here, where visiting the tied
+    # lanes one by one took 57.4
+    rand = torch.randn(8192, 256, generator=torch.Generator(device=dev).manual_seed(1), device=dev)
+    ids = torch.empty(8192, 8, dtype=torch.int32, device=dev)
+    w = torch.empty(8192, 8, device=dev)
+
+    def best_ms(lg):
+        best = float("inf")
+        for _ in range(6):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(50):
+                moe.moe_gate_topk(lg, 8, topk_ids=ids, topk_w=w)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) / 50)
+        return best
+
+    t_rand, t_equal = best_ms(rand), best_ms(torch.zeros_like(rand))
+    print(f"  gate of 8192 x 256: {1e3 * t_rand:.1f} us, equal logits {1e3 * t_equal:.1f} us", flush=True)
+    assert t_equal <= 2.0 * t_rand
+
+
 @pytest.mark.parametrize("E,k", [(48, 6), (128, 8), (300, 12)])
 @pytest.mark.parametrize("mode", ["softmax", "sigmoid"])
 def test_gate_masked_experts(dev, E, k, mode):
