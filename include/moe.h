@@ -297,9 +297,10 @@ moe_status moe_forward(const moe_args* a, void* ws, size_t ws_bytes, hipStream_t
 /*
  * moe_forward with per-stage timing: the same launches on the same stream,
  * with events[i] recorded before stage i and events[MOE_NUM_STAGES] after the
- * last stage.  Stages: 0 gate, 1 permute (empty up to 16 tokens and 256
- * experts, where the gate's launch does it), 2 fp8 activation quantisation or
- * int4 group sums (empty for bf16), 3 GEMM1 + SiLU*up, 4 GEMM2, 5 combine.
+ * last stage.  Stages: 0 gate, 1 permute (empty for small batches, at most 16
+ * tokens and 256 experts, whose gate's launch does it), 2 fp8 activation
+ * quantisation or int4 group sums of the hidden rows (empty for bf16), 3 GEMM1 +
+ * SiLU*up, 4 GEMM2 (int4: with the intermediate's group sums), 5 combine.
  *   events  host array of MOE_NUM_STAGES + 1 caller-created hipEvent_t; a
  *           NULL entry skips that mark (e.g. only GEMM1 bracketed: entries 3
  *           and 4 set)

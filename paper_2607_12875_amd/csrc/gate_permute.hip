@@ -6,9 +6,9 @@
 // Both steps are latency, most of it launch, first loads and the drain between
 // them, and the permute read back ids that the gate had just written: 16 tokens
 // took 7.1 + 5.8 us over 128 experts and 9.2 + 7.5 us over 256 in two launches,
-// 11.5 and 15.3 us in one (9.5 and 13.2 with the gate's later arg-max).  Up to one token per wave of the
-// workgroup (16), so the selection takes no longer than in its own launch;
-// above, the gate's tokens want more than one CU.
+// 11.5 and 15.3 us in one (9.5 and 13.2 with the gate's later arg-max).  One token per wave of the
+// workgroup; where one CU is too few for them, two launches are faster
+// (gate_permute_fits).
 #include "block_scan.hpp"
 #include "gate_select.hpp"
 #include "launch.hpp"
@@ -114,13 +114,24 @@ __global__ __launch_bounds__(kPermThreads) void gate_permute_kernel(
   inv_pos[tid] = pos;
 }
 
-bool gate_permute_fits(int T, int E, int k) { return T >= 1 && T <= kGpMaxT && E <= kGpMaxE && k <= MOE_GATE_MAX_K; }
+// Up to 8 tokens (two waves per SIMD) one launch is always the faster form: the
+// whole layer, H = 256, I = 128, 8 tokens: 8 experts, top 2, 17.9 us, in two launches 20.1;
+// 256 experts, top 8, 24.4 and 28.2, top 32, 64.7 and 67.4; with a router 23.7 and
+// 24.3, 31.9 and 34.6, 72.9 and 73.6.  From 9 to 16 tokens the arg-max rounds of
+// up to four waves per SIMD get in each other's way (16 tokens, 256 experts: top
+// 8 34.6 and 36.4, top 12 50.0 and 50.2, top 16 56.7 and 55.6, top 32 85.4 and
+// 77.3; rank selection up to 64 experts, top 32, 37.7 and 38.6), and so do the
+// loads of the router's slices (8 experts 25.5 and 24.8, 256 experts, top 8, 46.7 and 43.3).
+bool gate_permute_fits(int T, int E, int k, bool router) {
+  if (T < 1 || T > kGpMaxT || E > kGpMaxE || k > MOE_GATE_MAX_K) return false;
+  return T <= 8 || (!router && (E <= 64 || k <= 12));
+}
 
 hipError_t launch_gate_permute(const float* lg, int KS, const float* bias, int T, int E, int k, int mode, int renorm,
                                float scale, float* logits_out, int32_t* ids, float* w, int32_t* ids2, float* w2,
                                int block_m, int32_t* offsets, int32_t* sorted_ids, int32_t* inv_pos, int cap,
                                hipStream_t s) {
-  if (!gate_permute_fits(T, E, k) || KS < 0 || KS > kGpMaxKS) return hipErrorInvalidValue;
+  if (!gate_permute_fits(T, E, k, KS > 0) || KS < 0 || KS > kGpMaxKS) return hipErrorInvalidValue;
   const int epl = (E + 63) / 64;
 #define MOE_GP_CASE(N, P)                                                                                         \
   hipLaunchKernelGGL((gate_permute_kernel<N, P>), dim3(1), dim3(kPermThreads), 0, s, lg, KS, bias, T, E, k, mode, \

@@ -25,7 +25,7 @@ hipError_t launch_router_partial(const uint16_t* hidden, const uint16_t* wr, int
 
 // Gate (on logits [T,E] with KS = 0, or on KS router partials) and permute in
 // one launch, where gate_permute_fits.
-bool gate_permute_fits(int T, int E, int k);
+bool gate_permute_fits(int T, int E, int k, bool router);
 hipError_t launch_gate_permute(const float* lg, int KS, const float* bias, int T, int E, int k, int mode, int renorm,
                                float scale, float* logits_out, int32_t* ids, float* w, int32_t* ids2, float* w2,
                                int block_m, int32_t* offsets, int32_t* sorted_ids, int32_t* inv_pos, int cap,

@@ -260,7 +260,7 @@ moe_status run_layer(const moe_args* a, void* ws, size_t ws_bytes, hipEvent_t* e
 
   if (!mark(0)) return MOE_ERR_HIP;
   void* const router_ws = a->w_router ? at<void>(ws, L.router_ws) : nullptr;
-  if (moe::gate_permute_fits(a->T, a->E, a->top_k)) {
+  if (moe::gate_permute_fits(a->T, a->E, a->top_k, a->w_router != nullptr)) {
     // a small batch: selection and permute in one launch (the permute stage is empty)
     const float* lg = a->logits;
     int KS = 0;

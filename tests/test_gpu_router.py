@@ -118,3 +118,48 @@ def test_forward_with_router(dev, n, T, over):
     err = rel_err(out.float().cpu().numpy().astype(np.float64), ref["out"])
     print(f"  max|err|/rms = {err:.3e}", flush=True)
     assert err <= TOL[cfg.wfmt]
+
+
+@pytest.mark.parametrize("T", [1, 8, 9, 16])
+@pytest.mark.parametrize("n,E", [(2, 64), (2, 65), (2, 100), (2, 256), (4, 100), (4, 256)])
+def test_small_batches_with_router(dev, T, n, E):
+    # up to 8 tokens and 256 experts the K slices' sum, the gate and the
+    # permute are one launch (one lane per expert, two and four), above two: the
+    # selection and the permutation bit-exact on the logits the call returns,
+    # the optional outputs the same as the workspace's, and the call
+    # without them the same as with
+    cfg = synth.tiny_config(n, T=T, H=1152, E=E, I=128, top_k=min(8, E))
+    print(f"small batch with router {cfg}", flush=True)
+    inp = synth.make_inputs(cfg)
+    wr = synth.make_router_weights(cfg)
+    d = synth.to_device(inp)
+    k = cfg.top_k
+
+    def run(**outs):
+        out, ws = moe.moe_forward(d["hidden"], None, d["w1"], d["w2"], k, mode=cfg.mode, renormalize=cfg.renormalize,
+                                  routed_scale=cfg.routed_scale, wfmt=cfg.wfmt, sel_bias=d["sel_bias"],
+                                  w1_scale=d["w1_scale"], w2_scale=d["w2_scale"], w_router=_bf16(wr, dev), **outs)
+        torch.cuda.synchronize()
+        return out, ws
+
+    logits = torch.full((T, E), float("nan"), dtype=torch.float32, device=dev)
+    ids = torch.full((T, k), -1, dtype=torch.int32, device=dev)
+    wts = torch.full((T, k), float("nan"), dtype=torch.float32, device=dev)
+    out, ws = run(logits_out=logits, topk_ids_out=ids, topk_w_out=wts)
+    lg, ids, wts = logits.cpu().numpy(), ids.cpu().numpy(), wts.cpu().numpy()
+    assert np.all(np.abs(lg - O.router_logits(inp["hidden"], wr)) <= _bound(inp["hidden"], wr))
+    rid, rw = O.gate(lg, inp["sel_bias"], k, cfg.mode, cfg.renormalize, cfg.routed_scale)
+    assert np.array_equal(ids, rid)
+    assert np.all(np.abs(wts - rw) <= 1e-6 * np.abs(rw))
+    L = moe.moe_workspace_layout(moe.make_args(T, cfg.H, E, cfg.I, k, wfmt=cfg.wfmt, w_router=_bf16(wr, dev)))
+    assert np.array_equal(ws_view(ws, L, "topk_ids", torch.int32, T * k).reshape(T, k), ids)
+    assert np.array_equal(ws_view(ws, L, "topk_w", torch.float32, T * k).reshape(T, k), wts)
+    ro, rs, ri = O.permute(rid, E, L["block_m"])
+    assert np.array_equal(ws_view(ws, L, "expert_offsets", torch.int32, E + 1), ro)
+    assert np.array_equal(ws_view(ws, L, "sorted_ids", torch.int32, L["cap"]), rs)
+    assert np.array_equal(ws_view(ws, L, "inv_pos", torch.int32, T * k), ri)
+    err = rel_err(out.float().cpu().numpy().astype(np.float64), O.forward(cfg, dict(inp, logits=lg))["out"])
+    print(f"  max|err|/rms = {err:.3e}", flush=True)
+    assert err <= TOL[cfg.wfmt]
+    bare, _ = run()
+    assert torch.equal(out, bare)
