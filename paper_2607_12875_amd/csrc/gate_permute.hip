@@ -18,7 +18,6 @@ namespace moe {
 constexpr int kGpMaxT = kPermThreads / 64;
 constexpr int kGpMaxE = 256;
 constexpr int kGpMaxN = kGpMaxT * MOE_GATE_MAX_K;  // routed rows
-constexpr int kGpMaxKS = 32;                       // K slices of the router's partial logits
 
 // PART: the logits are the KS router partials lg[ks][T][E], summed in slice
 // order (and written to logits_out, if given); else lg is the logits [T][E].
@@ -50,14 +49,7 @@ __global__ __launch_bounds__(kPermThreads) void gate_permute_kernel(
       for (int i = 0; i < EPL; ++i) {
         const int e = lane + 64 * i;
         if (e >= E) continue;
-        // every slice requested before the first is added (slots past KS
-        // re-read the last slice and add +0: v is never -0)
-        float x[kGpMaxKS];
-#pragma unroll
-        for (int j = 0; j < kGpMaxKS; ++j) x[j] = lg[(static_cast<size_t>(min(j, KS - 1)) * T + wv) * E + e];
-        float v = 0.f;
-#pragma unroll
-        for (int j = 0; j < kGpMaxKS; ++j) v += j < KS ? x[j] : 0.f;
+        const float v = sum_slices<kRouterMaxKS>(row + e, KS, static_cast<size_t>(T) * E);
         slg[wv][e] = v;  // read back below by this same lane only
         if (logits_out) logits_out[static_cast<size_t>(wv) * E + e] = v;
       }
@@ -98,9 +90,7 @@ __global__ __launch_bounds__(kPermThreads) void gate_permute_kernel(
     }
   }
   __syncthreads();
-  for (int e = wv; e < E; e += NW)
-    for (int p = pad_begin[e] + lane; p < pad_end[e]; p += 64) sorted_ids[p] = n;
-  for (int p = total_padded + tid; p < cap; p += kPermThreads) sorted_ids[p] = n;
+  write_pads(pad_begin, pad_end, E, total_padded, cap, n, sorted_ids, 0, 1);
   if (tid >= n) return;
   if (my_e < 0) {
     inv_pos[tid] = -1;
@@ -131,7 +121,7 @@ hipError_t launch_gate_permute(const float* lg, int KS, const float* bias, int T
                                float scale, float* logits_out, int32_t* ids, float* w, int32_t* ids2, float* w2,
                                int block_m, int32_t* offsets, int32_t* sorted_ids, int32_t* inv_pos, int cap,
                                hipStream_t s) {
-  if (!gate_permute_fits(T, E, k, KS > 0) || KS < 0 || KS > kGpMaxKS) return hipErrorInvalidValue;
+  if (!gate_permute_fits(T, E, k, KS > 0) || KS < 0 || KS > kRouterMaxKS) return hipErrorInvalidValue;
   const int epl = (E + 63) / 64;
 #define MOE_GP_CASE(N, P)                                                                                         \
   hipLaunchKernelGGL((gate_permute_kernel<N, P>), dim3(1), dim3(kPermThreads), 0, s, lg, KS, bias, T, E, k, mode, \

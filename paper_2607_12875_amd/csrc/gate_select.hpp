@@ -110,6 +110,21 @@ __device__ __forceinline__ void gate_keys(const float* lg, const float* bias, in
   }
 }
 
+// One logit from its KS K-slice partials (at most MAX), `slice` elements apart, summed in
+// slice order.  Every slice is requested before the first is added (one
+// memory round trip; slots past KS re-read the last slice, so there is no
+// branch between the loads, and add +0: v is never -0).
+template <int MAX>
+__device__ __forceinline__ float sum_slices(const float* part, int KS, size_t slice) {
+  float x[MAX];
+#pragma unroll
+  for (int j = 0; j < MAX; ++j) x[j] = part[min(j, KS - 1) * slice];
+  float v = 0.f;
+#pragma unroll
+  for (int j = 0; j < MAX; ++j) v += j < KS ? x[j] : 0.f;
+  return v;
+}
+
 // Arg-max selection: k rounds of a cross-lane arg-max over the keys held in
 // registers.  Its work per token grows with k * log2(64), not with E, so it
 // wins once there are many experts per lane.  lg: this token's E logits;

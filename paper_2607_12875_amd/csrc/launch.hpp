@@ -19,7 +19,9 @@ hipError_t launch_router_gate(const uint16_t* hidden, const uint16_t* wr, int T,
                               int renorm, float scale, const float* bias, float* logits_out, int32_t* ids,
                               float* w, int32_t* ids2, float* w2, void* ws, hipStream_t s);
 
-// The router's logits as K-slice partials [KS][T][E] in ws (up to 1024 tokens): returns KS in *ks.
+// The router's logits as K-slice partials [KS][T][E] in ws (up to 1024 tokens): returns KS,
+// at most kRouterMaxKS, in *ks.
+constexpr int kRouterMaxKS = 32;
 hipError_t launch_router_partial(const uint16_t* hidden, const uint16_t* wr, int T, int H, int E, void* ws, int* ks,
                                  hipStream_t s);
 

@@ -108,13 +108,7 @@ __global__ __launch_bounds__(kPermThreads) void permute_scatter_kernel(
     if (tid == E - 1) offsets[E] = incl;
   }
   __syncthreads();
-  // pads: a wave per segment and the tail up to the capacity, both spread over
-  // the chunks' workgroups (a thread per segment in one workgroup wrote up to
-  // block_m - 1 pads one after the other: 16 us for 300 tokens, 256 experts and
-  // 128-row tiles, 6.8 this way)
-  for (int e = c * (kPermThreads / 64) + (tid >> 6); e < E; e += nchunks * (kPermThreads / 64))
-    for (int p = pad_begin[e] + lane_id(); p < pad_end[e]; p += 64) sorted_ids[p] = n;
-  for (int p = total_padded + c * kPermThreads + tid; p < cap; p += nchunks * kPermThreads) sorted_ids[p] = n;
+  write_pads(pad_begin, pad_end, E, total_padded, cap, n, sorted_ids, c, nchunks);
 
   if (my_e >= 0) {
     const uint32_t* row = bitmap + my_e * W;  // 16-byte aligned: W is a multiple of 4

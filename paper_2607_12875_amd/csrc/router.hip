@@ -209,8 +209,6 @@ __global__ __launch_bounds__(256) void router_partial_kernel(const uint16_t* __r
 
 // One wave per token: logits = the KS partials summed in slice order (fp32),
 // written out if asked, then the gate's selection and weights on them.
-constexpr int kRouterMaxKS = 32;  // most K slices of the split router
-
 template <int EPL>
 __global__ __launch_bounds__(256) void router_select_kernel(const float* __restrict__ part, int KS, int T, int E,
                                                             int k, int mode, int renorm, float scale,
@@ -230,16 +228,8 @@ __global__ __launch_bounds__(256) void router_select_kernel(const float* __restr
   for (int i = 0; i < EPL; ++i) {
     const int e = lane + 64 * i;
     if (e >= E) continue;
-    // every slice's partial is requested before the first is added (one
-    // memory round trip; slots past KS re-read the last slice, so there is no
-    // branch between the loads), then they are added in slice order (adding
-    // +0 for the slots past KS leaves v unchanged: v is never -0)
-    float x[kRouterMaxKS];
-#pragma unroll
-    for (int j = 0; j < kRouterMaxKS; ++j) x[j] = part[(static_cast<size_t>(min(j, KS - 1)) * T + t) * E + e];
-    float v = 0.f;
-#pragma unroll
-    for (int j = 0; j < kRouterMaxKS; ++j) v += j < KS ? x[j] : 0.f;
+    const float v =
+        sum_slices<kRouterMaxKS>(part + static_cast<size_t>(t) * E + e, KS, static_cast<size_t>(T) * E);
     lg[wv][e] = v;  // read back below by this same lane only
     if (logits_out) logits_out[static_cast<size_t>(t) * E + e] = v;
   }
