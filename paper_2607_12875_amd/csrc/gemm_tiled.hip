@@ -107,8 +107,9 @@ __device__ __forceinline__ int swz_b(int r) { return BB == 32 ? (r >> 2) & 1 : B
 // (L1 waiting on L2) cannot hold up the MFMA stream behind an in-order copy
 // instruction.  NP == 0: the math waves issue the copies themselves.
 // SUMS (int4): the rows' group sums are there; else the bias comes off by MFMAs.
+// ONCE: experts with one row tile copy their weights with the non-temporal hint.
 template <int FMT, bool GEMM1, int BM, int BNW, int WM, int WN, int GM, int KBT = 128, int STAGES = 3, int NP = 0,
-          bool SUMS = true>
+          bool SUMS = true, bool ONCE = false>
 // The 64-row 4-bit GEMMs with copy waves are held to 128 registers, which keeps two workgroups per CU.
 __global__ __launch_bounds__((WM * WN + NP) * 64) __attribute__((amdgpu_waves_per_eu((FMT == 2 || FMT == 4) && (GEMM1 || NP > 0) && BM == 64 && KBT < 512 ? 4 : 1)))
 void moe_gemm_tiled(GroupedGemm g) {
@@ -211,7 +212,6 @@ void moe_gemm_tiled(GroupedGemm g) {
   };
 
   constexpr int NSL = SC > 0 ? SC : 1;
-  constexpr bool ONCE = FMT != 4 && !(FMT == 2 && KB == 256);  // non-temporal copies of weights read once (see sources)
   struct Src {
     const uint8_t* a[A_CH];  // A rows
     int am[A_CH];            // A step-advance mask: -1, or 0 for a pad row (its source is the zero chunk)
@@ -234,16 +234,11 @@ void moe_gemm_tiled(GroupedGemm g) {
     // copies the zero chunk at every step: one cache line per instruction
     // rather than a row's eight, and zeros in LDS; its products are never
     // read.  Scale sources of pad rows read the last token's.
-    // Weights of an expert with one row tile are read by one workgroup only:
-    // the non-temporal hint keeps them from displacing the rows that other
-    // tiles share in L2 (fp8, 7168 x 2048 x 256 experts, top 8, 300 tokens: the
-    // layer 1257 us without, 1218 with; bf16, 777 tokens 493 and 477; int4, 512
-    // tokens 365 and 359).  With two or more row tiles the hint costs the
-    // sharing (prefill GEMM1 675 -> 973 us with it everywhere).  The 128-element
-    // int4 steps, whose registers are all taken, stay without, and so does
-    // MXFP4, where the choice cost the copy waves more (8192 tokens 6243 us
-    // without, 6332 with).  The choice is made once per step: one per copy
-    // cost the bf16 layer of 4096 tokens 7 %.
+    // Weights of an expert with one row tile are read once: the hint keeps
+    // them from displacing what other tiles share.  With two or more row tiles
+    // it costs the sharing (prefill GEMM1 675 -> 973 us with it everywhere).
+    // Chosen once per step: a choice per copy cost the bf16 layer of 4096
+    // tokens 7 %.
     src.once = ONCE && __builtin_amdgcn_readfirstlane(lds_off[e + 1] - lds_off[e]) == BM;
     int sid[A_CH + NSL];
 #pragma unroll
@@ -1461,7 +1456,7 @@ dim3 persistent_grid(int per_cu, long max_tiles) {
 }
 
 template <int FMT, bool GEMM1, int BM, int BNW, int WM, int WN, int GM, int KBT = 128, int STAGES = 3, int NP = 0,
-          bool SUMS = true>
+          bool SUMS = true, bool ONCE = false>
 hipError_t launch_tiled(const GroupedGemm& g, hipStream_t s) {
   constexpr int NC = GEMM1 ? BNW / 2 : BNW;
   constexpr int NT = (WM * WN + NP) * 64;
@@ -1470,7 +1465,7 @@ hipError_t launch_tiled(const GroupedGemm& g, hipStream_t s) {
   constexpr int KE = (FMT == 1 || FMT == 5) ? KBT : KBT / 2;
   if (FMT != 0 && (GEMM1 ? g.H : g.I) % KE != 0) return hipErrorInvalidValue;
   const long mt = g.max_rows / BM, nt = ((GEMM1 ? g.I : g.H) + NC - 1) / NC;
-  auto kern = moe_gemm_tiled<FMT, GEMM1, BM, BNW, WM, WN, GM, KBT, STAGES, NP, SUMS>;
+  auto kern = moe_gemm_tiled<FMT, GEMM1, BM, BNW, WM, WN, GM, KBT, STAGES, NP, SUMS, ONCE>;
   // workgroups per CU depend on the kernel's registers and LDS only: queried
   // once per instantiation (thread-safe static initialisation)
   static const int per_cu = occupancy_per_cu(kern, NT);
@@ -1479,6 +1474,21 @@ hipError_t launch_tiled(const GroupedGemm& g, hipStream_t s) {
 }
 
 }  // namespace
+
+// Whether the weights of experts with one row tile are copied with the
+// non-temporal hint, for bf16 and fp8: where experts have at most a tile of rows on
+// average.  Layers without and with it, the same weights as in the call before and,
+// second, after 1 GB of other reads: bf16, 4096 x 1408 x 64 experts, top 6, 777
+// tokens (73 rows per expert) 495 -> 473 us, -4.3 %; 1200 (112) -1.2 %, -0.8 %; 2500 (234)
+// +0.2 %, +0.8 %; 4096 (384) +0.7 %, +0.8 %, the choice alone; fp8, 7168 x 2048 x 256
+// experts, top 8, 300 tokens (9) 1245 -> 1162, -6.2 %; 4000 (125) -0.7 %, -1.0 %.  The
+// 256-element int4 steps always take it, for little: 4096 x 1536 x 128 experts, top 8,
+// 512 tokens -1.5 %, +0.4 %, 2048 -0.7 %, -1.7 %, 5120 x 1536 x 160, top 6, 200 tokens +0.9 %,
+// +2.0 %.  MXFP4 x MXFP8 has no use for it: 2048 x 1408 x 60 experts, top 4, 260
+// tokens +14 %, +2.5 % (weights that the memory-side cache held from call to call no
+// longer stay there), 7168 x 2048 x 256, 1000 tokens -0.1 %, +0.1 %.  Nor has MXFP4, as far
+// as measured (8192 tokens 6243 -> 6332 us).
+bool weights_once(const GroupedGemm& g) { return g.n_routed <= 128L * g.E; }
 
 // bf16 tile shapes: rows x weight rows per workgroup, waves as WM x WN.
 #ifndef MOE_T1_BNW
@@ -1523,12 +1533,17 @@ hipError_t launch_tiled(const GroupedGemm& g, hipStream_t s) {
 #define MOE_TGM_INT4 16
 #endif
 int bf16_tiled_block_m() { return MOE_TBF_BM; }
+template <bool GEMM1, int BNW, int WM, int WN, int NP>
+hipError_t launch_bf16(const GroupedGemm& g, hipStream_t s) {
+  if (weights_once(g)) return launch_tiled<0, GEMM1, MOE_TBF_BM, BNW, WM, WN, MOE_TGM, MOE_TBF_KB, MOE_TBF_STAGES, NP, true, true>(g, s);
+  return launch_tiled<0, GEMM1, MOE_TBF_BM, BNW, WM, WN, MOE_TGM, MOE_TBF_KB, MOE_TBF_STAGES, NP>(g, s);
+}
 hipError_t launch_gemm1_bf16_tiled(const GroupedGemm& g, hipStream_t s) {
-  return launch_tiled<0, true, MOE_TBF_BM, MOE_T1_BNW, MOE_T1_WM, MOE_T1_WN, MOE_TGM, MOE_TBF_KB, MOE_TBF_STAGES, MOE_TBF_NP1>(g, s);
+  return launch_bf16<true, MOE_T1_BNW, MOE_T1_WM, MOE_T1_WN, MOE_TBF_NP1>(g, s);
 }
 hipError_t launch_gemm2_bf16_tiled(const GroupedGemm& g, hipStream_t s) {
-  if (g.H % MOE_T2_BNW) return launch_tiled<0, false, MOE_TBF_BM, 128, MOE_T2_WM, MOE_T2_WN, MOE_TGM, MOE_TBF_KB, MOE_TBF_STAGES, MOE_TBF_NP2>(g, s);
-  return launch_tiled<0, false, MOE_TBF_BM, MOE_T2_BNW, MOE_T2_WM, MOE_T2_WN, MOE_TGM, MOE_TBF_KB, MOE_TBF_STAGES, MOE_TBF_NP2>(g, s);
+  if (g.H % MOE_T2_BNW) return launch_bf16<false, 128, MOE_T2_WM, MOE_T2_WN, MOE_TBF_NP2>(g, s);
+  return launch_bf16<false, MOE_T2_BNW, MOE_T2_WM, MOE_T2_WN, MOE_TBF_NP2>(g, s);
 }
 
 // fp8 over the 128 x 256 tile: with copy waves (NP > 0) four math waves
@@ -1546,8 +1561,10 @@ hipError_t launch_gemm2_bf16_tiled(const GroupedGemm& g, hipStream_t s) {
 int gemm_block_m_fp8(int, int, int) { return 128; }
 template <bool GEMM1, int BNW, int NP>
 hipError_t launch_fp8(const GroupedGemm& g, hipStream_t s) {
-  if constexpr (NP > 0) return launch_tiled<1, GEMM1, 128, BNW, 1, 4, MOE_TGM, 128, 3, NP>(g, s);
-  else return launch_tiled<1, GEMM1, 128, BNW, MOE_F8_WM, MOE_F8_WN, MOE_TGM>(g, s);
+  if constexpr (NP > 0) {
+    if (weights_once(g)) return launch_tiled<1, GEMM1, 128, BNW, 1, 4, MOE_TGM, 128, 3, NP, true, true>(g, s);
+    return launch_tiled<1, GEMM1, 128, BNW, 1, 4, MOE_TGM, 128, 3, NP>(g, s);
+  } else return launch_tiled<1, GEMM1, 128, BNW, MOE_F8_WM, MOE_F8_WN, MOE_TGM>(g, s);
 }
 hipError_t launch_gemm1_fp8(const GroupedGemm& g, hipStream_t s) {
   return launch_fp8<true, 256, MOE_F8_NP1>(g, s);
@@ -1598,7 +1615,7 @@ template <bool GEMM1, int BNW>
 hipError_t launch_int4(const GroupedGemm& g, hipStream_t s) {
   if constexpr (!GEMM1)
     if (!g.inter_sums) return launch_tiled<2, false, MOE_TI4_BM, BNW, 1, 4, MOE_TGM_INT4, MOE_TI4_KB, MOE_TI4_STAGES, MOE_TI4_NP2, false>(g, s);
-  if (int4_long_steps<GEMM1, BNW>(g)) return launch_tiled<2, GEMM1, MOE_TI4_BM, BNW, 1, 4, MOE_TGM_INT4, 512, 2, 4>(g, s);
+  if (int4_long_steps<GEMM1, BNW>(g)) return launch_tiled<2, GEMM1, MOE_TI4_BM, BNW, 1, 4, MOE_TGM_INT4, 512, 2, 4, true, true>(g, s);
   return launch_tiled<2, GEMM1, MOE_TI4_BM, BNW, 1, 4, MOE_TGM_INT4, MOE_TI4_KB, MOE_TI4_STAGES, GEMM1 ? MOE_TI4_NP1 : MOE_TI4_NP2>(g, s);
 }
 hipError_t launch_gemm1_int4(const GroupedGemm& g, hipStream_t s) { return launch_int4<true, 256>(g, s); }
