@@ -106,10 +106,12 @@ __device__ __forceinline__ int swz_b(int r) { return BB == 32 ? (r >> 2) & 1 : B
 // waves never touch global memory in the main loop, so a stalled load queue
 // (L1 waiting on L2) cannot hold up the MFMA stream behind an in-order copy
 // instruction.  NP == 0: the math waves issue the copies themselves.
-// SUMS (int4): the rows' group sums are there; else the bias comes off by MFMAs.
-// ONCE: experts with one row tile copy their weights with the non-temporal hint.
+// OPT, a sum of: kNoSums (int4: no group sums of the rows are there, the bias comes
+// off by MFMAs), kOnce (experts with one row tile copy their weights with the
+// non-temporal hint).
+constexpr int kNoSums = 1, kOnce = 2;
 template <int FMT, bool GEMM1, int BM, int BNW, int WM, int WN, int GM, int KBT = 128, int STAGES = 3, int NP = 0,
-          bool SUMS = true, bool ONCE = false>
+          int OPT = 0>
 // The 64-row 4-bit GEMMs with copy waves are held to 128 registers, which keeps two workgroups per CU.
 __global__ __launch_bounds__((WM * WN + NP) * 64) __attribute__((amdgpu_waves_per_eu((FMT == 2 || FMT == 4) && (GEMM1 || NP > 0) && BM == 64 && KBT < 512 ? 4 : 1)))
 void moe_gemm_tiled(GroupedGemm g) {
@@ -120,6 +122,7 @@ void moe_gemm_tiled(GroupedGemm g) {
   static_assert(NP == 0 || WM * WN == 4, "split launches have one math wave per SIMD");
   constexpr bool F4B = FMT == 2 || FMT == 4;  // 4-bit weights (int4, MXFP4), bf16 activations
   constexpr bool MX8 = FMT == 5;              // MXFP4 weights, MXFP8 activations
+  constexpr bool SUMS = !(OPT & kNoSums), ONCE = OPT & kOnce;
   constexpr bool A8 = FMT == 1 || MX8;        // one-byte (e4m3) activations
   constexpr bool B4 = F4B || MX8;             // 4-bit weight rows
   static_assert(KBT == 128 || (KBT == 64 && FMT == 0) || (KBT == 256 && (F4B || FMT == 5)) || (KBT == 512 && FMT == 2 && NP > 0),
@@ -1456,7 +1459,7 @@ dim3 persistent_grid(int per_cu, long max_tiles) {
 }
 
 template <int FMT, bool GEMM1, int BM, int BNW, int WM, int WN, int GM, int KBT = 128, int STAGES = 3, int NP = 0,
-          bool SUMS = true, bool ONCE = false>
+          int OPT = 0>
 hipError_t launch_tiled(const GroupedGemm& g, hipStream_t s) {
   constexpr int NC = GEMM1 ? BNW / 2 : BNW;
   constexpr int NT = (WM * WN + NP) * 64;
@@ -1465,7 +1468,7 @@ hipError_t launch_tiled(const GroupedGemm& g, hipStream_t s) {
   constexpr int KE = (FMT == 1 || FMT == 5) ? KBT : KBT / 2;
   if (FMT != 0 && (GEMM1 ? g.H : g.I) % KE != 0) return hipErrorInvalidValue;
   const long mt = g.max_rows / BM, nt = ((GEMM1 ? g.I : g.H) + NC - 1) / NC;
-  auto kern = moe_gemm_tiled<FMT, GEMM1, BM, BNW, WM, WN, GM, KBT, STAGES, NP, SUMS, ONCE>;
+  auto kern = moe_gemm_tiled<FMT, GEMM1, BM, BNW, WM, WN, GM, KBT, STAGES, NP, OPT>;
   // workgroups per CU depend on the kernel's registers and LDS only: queried
   // once per instantiation (thread-safe static initialisation)
   static const int per_cu = occupancy_per_cu(kern, NT);
@@ -1535,7 +1538,7 @@ bool weights_once(const GroupedGemm& g) { return g.n_routed <= 128L * g.E; }
 int bf16_tiled_block_m() { return MOE_TBF_BM; }
 template <bool GEMM1, int BNW, int WM, int WN, int NP>
 hipError_t launch_bf16(const GroupedGemm& g, hipStream_t s) {
-  if (weights_once(g)) return launch_tiled<0, GEMM1, MOE_TBF_BM, BNW, WM, WN, MOE_TGM, MOE_TBF_KB, MOE_TBF_STAGES, NP, true, true>(g, s);
+  if (weights_once(g)) return launch_tiled<0, GEMM1, MOE_TBF_BM, BNW, WM, WN, MOE_TGM, MOE_TBF_KB, MOE_TBF_STAGES, NP, kOnce>(g, s);
   return launch_tiled<0, GEMM1, MOE_TBF_BM, BNW, WM, WN, MOE_TGM, MOE_TBF_KB, MOE_TBF_STAGES, NP>(g, s);
 }
 hipError_t launch_gemm1_bf16_tiled(const GroupedGemm& g, hipStream_t s) {
@@ -1562,7 +1565,7 @@ int gemm_block_m_fp8(int, int, int) { return 128; }
 template <bool GEMM1, int BNW, int NP>
 hipError_t launch_fp8(const GroupedGemm& g, hipStream_t s) {
   if constexpr (NP > 0) {
-    if (weights_once(g)) return launch_tiled<1, GEMM1, 128, BNW, 1, 4, MOE_TGM, 128, 3, NP, true, true>(g, s);
+    if (weights_once(g)) return launch_tiled<1, GEMM1, 128, BNW, 1, 4, MOE_TGM, 128, 3, NP, kOnce>(g, s);
     return launch_tiled<1, GEMM1, 128, BNW, 1, 4, MOE_TGM, 128, 3, NP>(g, s);
   } else return launch_tiled<1, GEMM1, 128, BNW, MOE_F8_WM, MOE_F8_WN, MOE_TGM>(g, s);
 }
@@ -1614,8 +1617,8 @@ bool int4_long_steps(const GroupedGemm& g) {
 template <bool GEMM1, int BNW>
 hipError_t launch_int4(const GroupedGemm& g, hipStream_t s) {
   if constexpr (!GEMM1)
-    if (!g.inter_sums) return launch_tiled<2, false, MOE_TI4_BM, BNW, 1, 4, MOE_TGM_INT4, MOE_TI4_KB, MOE_TI4_STAGES, MOE_TI4_NP2, false>(g, s);
-  if (int4_long_steps<GEMM1, BNW>(g)) return launch_tiled<2, GEMM1, MOE_TI4_BM, BNW, 1, 4, MOE_TGM_INT4, 512, 2, 4, true, true>(g, s);
+    if (!g.inter_sums) return launch_tiled<2, false, MOE_TI4_BM, BNW, 1, 4, MOE_TGM_INT4, MOE_TI4_KB, MOE_TI4_STAGES, MOE_TI4_NP2, kNoSums>(g, s);
+  if (int4_long_steps<GEMM1, BNW>(g)) return launch_tiled<2, GEMM1, MOE_TI4_BM, BNW, 1, 4, MOE_TGM_INT4, 512, 2, 4, kOnce>(g, s);
   return launch_tiled<2, GEMM1, MOE_TI4_BM, BNW, 1, 4, MOE_TGM_INT4, MOE_TI4_KB, MOE_TI4_STAGES, GEMM1 ? MOE_TI4_NP1 : MOE_TI4_NP2>(g, s);
 }
 hipError_t launch_gemm1_int4(const GroupedGemm& g, hipStream_t s) { return launch_int4<true, 256>(g, s); }

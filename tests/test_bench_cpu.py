@@ -3,8 +3,14 @@ dominant kernel out of rocprofv3 output, the counter-to-bytes scaling, and
 the code-only source hash the committed counter summaries are keyed to."""
 import csv
 import os
+import re
+import shutil
+import subprocess
+
+import pytest
 
 import bench
+import paper_2607_12875_amd as moe
 
 
 def test_code_only_ignores_comments_and_whitespace():
@@ -28,6 +34,17 @@ def test_gemm1_kernel_match():
           "void moe::combine_kernel<true, false, 6>(void const*, float const*, int const*, int, int, int, void*)"]
     assert all(bench.gemm1_kernel_match(n) for n in yes)
     assert not any(bench.gemm1_kernel_match(n) for n in no)
+
+
+@pytest.mark.skipif(shutil.which("nm") is None, reason="lists the library's symbols with nm")
+def test_gemm1_kernel_match_on_the_library():
+    # the tiled kernels that the library holds: the second template argument
+    # is the product
+    out = subprocess.run(["nm", "-C", moe._binding.LIB_PATH], capture_output=True, text=True, check=True).stdout
+    names = set(re.findall(r"moe::moe_gemm_tiled<[^>]*>", out))
+    assert len(names) >= 10
+    for n in names:
+        assert bench.gemm1_kernel_match(f"void {n}(moe::GroupedGemm)") == (n.split(", ")[1] == "true"), n
 
 
 def _write(path, rows):
