@@ -102,31 +102,28 @@ __device__ __forceinline__ int swz(int r) { return KB >= 256 ? r & 15 : KB == 12
 template <int BB>
 __device__ __forceinline__ int swz_b(int r) { return BB == 32 ? (r >> 2) & 1 : BB == 64 ? (r >> 2) & 3 : (r >> 1) & 7; }
 
-// NP > 0: NP extra waves only issue the global->LDS copies and the NW math
-// waves never touch global memory in the main loop, so a stalled load queue
+// Four math waves, one per SIMD and side by side in the tile's columns, and four
+// copy waves.  Only the copy waves issue the global->LDS copies and the math waves
+// never touch global memory in the main loop, so a stalled load queue
 // (L1 waiting on L2) cannot hold up the MFMA stream behind an in-order copy
-// instruction.  NP == 0: the math waves issue the copies themselves.
+// instruction.
 // OPT, a sum of: kNoSums (int4: no group sums of the rows are there, the bias comes
 // off by MFMAs), kOnce (experts with one row tile copy their weights with the
 // non-temporal hint).
 constexpr int kNoSums = 1, kOnce = 2;
-template <int FMT, bool GEMM1, int BM, int BNW, int WM, int WN, int GM, int KBT = 128, int STAGES = 3, int NP = 0,
-          int OPT = 0>
-// The 64-row 4-bit GEMMs with copy waves are held to 128 registers, which keeps two workgroups per CU.
-__global__ __launch_bounds__((WM * WN + NP) * 64) __attribute__((amdgpu_waves_per_eu((FMT == 2 || FMT == 4) && (GEMM1 || NP > 0) && BM == 64 && KBT < 512 ? 4 : 1)))
+constexpr int kMathWaves = 4, kCopyWaves = 4;
+template <int FMT, bool GEMM1, int BM, int BNW, int GM, int KBT, int STAGES, int OPT = 0>
+// The 128-element int4 steps are held to 128 registers, which keeps two workgroups per CU.
+__global__ __launch_bounds__((kMathWaves + kCopyWaves) * 64) __attribute__((amdgpu_waves_per_eu(FMT == 2 && KBT < 512 ? 4 : 1)))
 void moe_gemm_tiled(GroupedGemm g) {
-  constexpr int NW = WM * WN, NT = (NW + NP) * 64;
-  constexpr int LW = NP > 0 ? NP : NW;  // waves that issue the copies
-  static_assert(NW == 4 || NW == 8, "four or eight math waves");
-  static_assert(NP == 0 || NW % NP == 0, "scale slots split evenly over the copy waves");
-  static_assert(NP == 0 || WM * WN == 4, "split launches have one math wave per SIMD");
+  constexpr int NW = kMathWaves, WN = NW, NT = (NW + kCopyWaves) * 64;
+  constexpr int LW = kCopyWaves;
   constexpr bool F4B = FMT == 2 || FMT == 4;  // 4-bit weights (int4, MXFP4), bf16 activations
   constexpr bool MX8 = FMT == 5;              // MXFP4 weights, MXFP8 activations
   constexpr bool SUMS = !(OPT & kNoSums), ONCE = OPT & kOnce;
   constexpr bool A8 = FMT == 1 || MX8;        // one-byte (e4m3) activations
   constexpr bool B4 = F4B || MX8;             // 4-bit weight rows
-  static_assert(KBT == 128 || (KBT == 64 && FMT == 0) || (KBT == 256 && (F4B || FMT == 5)) || (KBT == 512 && FMT == 2 && NP > 0),
-                "64-byte steps are bf16 only, 256-byte steps 4-bit weights only, 512-byte steps int4 only");
+  static_assert(FMT == 2 ? KBT == 256 || KBT == 512 : FMT == 4 ? KBT == 256 : MX8 ? KBT == 128 || KBT == 256 : KBT == 128, "step");
   constexpr int KB = KBT;                                       // A bytes per row per step
   constexpr int KE = A8 ? KB : KB / 2;                                 // K elements per step
   constexpr int BB = B4 ? KE / 2 : KB;                                 // B bytes per row per step
@@ -135,15 +132,14 @@ void moe_gemm_tiled(GroupedGemm g) {
   // y stores, one pad check per row; bf16 prefill 4 % faster, GEMM1 was not)
   constexpr bool TRB = !A8 && !GEMM1 && FMT != 2;
   constexpr int RPI = 1024 / KB, LPR = KB / 16;  // rows per DMA instruction, lanes per row
-  constexpr int WTM = BM / WM, WTN = BNW / WN;
-  constexpr int TM = WTM / 32, TN = WTN / 32;
+  constexpr int WTN = BNW / WN;
+  constexpr int TM = BM / 32, TN = WTN / 32;
   constexpr int NC = GEMM1 ? BNW / 2 : BNW;  // output columns per tile
   // 16-byte DMA instructions per copy wave per stage (each moves 1 KB)
   constexpr int A_CH = BM * KB / 1024 / LW, B_CH = BNW * BB / 1024 / LW;
   static_assert(A_CH >= 1 && B_CH >= 1 && A_CH * LW * 1024 == BM * KB && B_CH * LW * 1024 == BNW * BB, "");
   static_assert(!GEMM1 || TN % 2 == 0, "gate/up pairs");
   static_assert(FMT != 1 || !GEMM1 || NC == 128, "fp8 requant needs one 128-column group per tile");
-  static_assert(!MX8 || (NP > 0 && WM * WN == 4), "MXFP8: four math waves beside copy waves");
   // per-stage scale block: NW slots of 256 bytes, one 4-byte DMA instruction
   // each (64 floats); fp8: slots [0, BM/64) the row scales of A, slot BM/64
   // the block scales of B; int4: slots [0, BNW/64) the bf16 pair holding each
@@ -160,9 +156,9 @@ void moe_gemm_tiled(GroupedGemm g) {
   constexpr int NSLOT = FMT == 0 ? 0 : (MX8 ? MXD * (BM + BNW) / 64 : (GSUM ? 2 : 1) * NW);
   constexpr int SC = (NSLOT + LW - 1) / LW;  // scale loads per copy wave per stage
   static_assert(FMT != 1 || BM / 64 < NW, "fp8 scale DMA layout");
-  static_assert(!F4B || (NW == 4 && BNW / 64 <= NW), "4-bit scale DMA layout");
+  static_assert(!F4B || BNW / 64 <= NW, "4-bit scale DMA layout");
   static_assert(!GSUM || (BNW / 64 + GD * BM / 64 <= 2 * NW && STAGES == 2), "int4 group-sum DMA layout");
-  static_assert(STAGES >= 2 && (STAGES - 2) * (A_CH + B_CH + SC) < 64, "vmcnt range");
+  static_assert(STAGES >= 2 && STAGES <= 4 && (STAGES - 2) * (A_CH + B_CH + SC) < 64, "vmcnt range");
   constexpr int A_BYTES = BM * KB, B_BYTES = BNW * BB, S_BYTES = SC * LW * 256;
   constexpr int STAGE = A_BYTES + B_BYTES + S_BYTES;
   constexpr int N_DMA = A_CH + B_CH + SC;  // loads per copy wave per stage
@@ -171,14 +167,12 @@ void moe_gemm_tiled(GroupedGemm g) {
   __shared__ float lds_amax[FMT == 1 && GEMM1 ? WN : 1][FMT == 1 && GEMM1 ? BM : 1];
   __shared__ int lds_off[MOE_MAX_EXPERTS_DEV + 1];  // expert_offsets, read once per workgroup
   // copy waves: the next tile's row ids, one slot per copy wave
-  __shared__ int lds_sid[NP > 0 ? NP : 1][NP > 0 ? BM : 1];
+  __shared__ int lds_sid[LW][BM];
 
   const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
-  const int wm = wave / WN, wn = wave % WN;
-  const bool is_math = wave < NW;                       // uniform per wave
-  const bool is_loader = NP == 0 || wave >= NW;
-  // copy-wave index (math waves of a split launch take 0: their sources stay in range, unused)
-  const int lw = NP > 0 ? (is_loader ? wave - NW : 0) : wave;
+  const int wn = wave % WN;
+  const bool is_math = wave < NW;             // uniform per wave
+  const int lw = is_math ? 0 : wave - NW;     // copy-wave index
   const int l32 = lane & 31, kg = lane >> 5;
   const int K = GEMM1 ? g.H : g.I;
   const int N = GEMM1 ? g.I : g.H;       // output columns of the product
@@ -247,8 +241,7 @@ void moe_gemm_tiled(GroupedGemm g) {
 #pragma unroll
     for (int i = 0; i < A_CH; ++i) {
       const int r = (i * LW + lw) * RPI + lane / LPR;
-      if constexpr (NP > 0) sid[i] = staged ? lds_sid[lw][r] : g.sorted_ids[m0 + r];
-      else sid[i] = g.sorted_ids[m0 + r];
+      sid[i] = staged ? lds_sid[lw][r] : g.sorted_ids[m0 + r];
     }
     if constexpr (GEMM1) {
 #pragma unroll
@@ -257,13 +250,11 @@ void moe_gemm_tiled(GroupedGemm g) {
         int v = 0;
         if (A8 && lw + k * LW < MXD * (BM / 64)) {
           const int ra = ((lw + k * LW) % (BM / 64)) * 64 + lane;  // A row of the slot
-          if constexpr (NP > 0) v = staged ? lds_sid[lw][ra] : g.sorted_ids[m0 + ra];
-          else v = g.sorted_ids[m0 + ra];
+          v = staged ? lds_sid[lw][ra] : g.sorted_ids[m0 + ra];
         }
         const int rg = (lw + k * LW - BNW / 64) % (BM / 64) * 64 + lane;  // group-sum slot row
         if (GSUM && lw + k * LW >= BNW / 64 && lw + k * LW < BNW / 64 + GD * BM / 64) {
-          if constexpr (NP > 0) v = staged ? lds_sid[lw][rg] : g.sorted_ids[m0 + rg];
-          else v = g.sorted_ids[m0 + rg];
+          v = staged ? lds_sid[lw][rg] : g.sorted_ids[m0 + rg];
         }
         sid[A_CH + k] = v;
       }
@@ -372,8 +363,7 @@ void moe_gemm_tiled(GroupedGemm g) {
     }
   };
 
-  // issue step kt of the tile `src` describes (DMA q in [q0, q1) of this copy
-  // wave's A_CH + B_CH tile loads, plus the scale loads with q1 == N_DMA)
+  // issue this copy wave's N_DMA loads of step kt of the tile `src` describes
   // into LDS buffer `buf`
   // bf16 ragged K: in the last step a lane whose 8-element chunk starts at
   // or past K copies the zero chunk instead (A row chunk (lane % LPR) ^ swz(r),
@@ -384,31 +374,29 @@ void moe_gemm_tiled(GroupedGemm g) {
     const int c = (lane % LPR) ^ swz<KB>(r);
     return kt * KE + 8 * c >= K ? static_cast<const uint8_t*>(kZeroChunk) : p;
   };
-  auto issue_part = [&](const Src& src, int kt, int buf, int q0, int q1) {
+  auto issue = [&](const Src& src, int kt, int buf) {
     const uint32_t base = smem0 + buf * STAGE;
     if (FMT == 0 && k_ragged && kt == nk - 1) {  // uniform: only the last step of a ragged K
 #pragma unroll
       for (int i = 0; i < A_CH; ++i)
-        if (i >= q0 && i < q1) dma16(tail_src(src.a[i] + (kt * KB & src.am[i]), i * LW + lw, kt), base + (i * LW + lw) * 1024);
+        dma16(tail_src(src.a[i] + (kt * KB & src.am[i]), i * LW + lw, kt), base + (i * LW + lw) * 1024);
 #pragma unroll
       for (int i = 0; i < B_CH; ++i)
-        if (A_CH + i >= q0 && A_CH + i < q1)
-          dma16(tail_src(src.b[i] + kt * BB, i * LW + lw, kt), base + A_BYTES + (i * LW + lw) * 1024);
+        dma16(tail_src(src.b[i] + kt * BB, i * LW + lw, kt), base + A_BYTES + (i * LW + lw) * 1024);
     } else {
 #pragma unroll
       for (int i = 0; i < A_CH; ++i)
-        if (i >= q0 && i < q1) dma16(src.a[i] + (kt * KB & src.am[i]), base + (i * LW + lw) * 1024);
+        dma16(src.a[i] + (kt * KB & src.am[i]), base + (i * LW + lw) * 1024);
       if (ONCE && src.once) {
 #pragma unroll
         for (int i = 0; i < B_CH; ++i)
-          if (A_CH + i >= q0 && A_CH + i < q1) dma16_nt(src.b[i] + kt * BB, base + A_BYTES + (i * LW + lw) * 1024);
+          dma16_nt(src.b[i] + kt * BB, base + A_BYTES + (i * LW + lw) * 1024);
       } else {
 #pragma unroll
         for (int i = 0; i < B_CH; ++i)
-          if (A_CH + i >= q0 && A_CH + i < q1) dma16(src.b[i] + kt * BB, base + A_BYTES + (i * LW + lw) * 1024);
+          dma16(src.b[i] + kt * BB, base + A_BYTES + (i * LW + lw) * 1024);
       }
     }
-    if (q1 < N_DMA) return;
 #pragma unroll
     for (int k = 0; k < SC; ++k) {
       // int4 (two stages, so every wait drains all loads and the
@@ -433,12 +421,9 @@ void moe_gemm_tiled(GroupedGemm g) {
       }
     }
   };
-  auto issue = [&](const Src& src, int kt, int buf) { issue_part(src, kt, buf, 0, N_DMA); };
   // this copy wave's loads for a step have landed once at most `ahead`
   // later steps (N_DMA loads each) are still in flight
   auto wait_ahead = [&](int ahead) {
-    if constexpr (STAGES >= 6) { if (ahead >= 4) { vm_wait<4 * N_DMA>(); return; } }
-    if constexpr (STAGES >= 5) { if (ahead == 3) { vm_wait<3 * N_DMA>(); return; } }
     if constexpr (STAGES >= 4) { if (ahead == 2) { vm_wait<2 * N_DMA>(); return; } }
     if constexpr (STAGES >= 3) { if (ahead == 1) { vm_wait<N_DMA>(); return; } }
     vm_wait<0>();
@@ -448,82 +433,71 @@ void moe_gemm_tiled(GroupedGemm g) {
   // sequence lives in LDS buffer s % STAGES; `sb` is the buffer of a tile's
   // step 0.  STAGES-1 steps are loaded ahead: step s+STAGES-1 goes into the
   // buffer read in step s-1, issued once the barrier of step s shows every
-  // wave is past it.  With copy waves the next tile's first STAGES-1 steps
+  // wave is past it.  The next tile's first STAGES-1 steps
   // are issued right after the barrier of the current tile's last step (their
   // buffers were read in earlier steps), so they load during that step and
-  // the epilogue; without, each tile starts with a barrier and the math
-  // waves load its first steps themselves.
+  // the epilogue.
   const int t0 = xcd * chunk + slot;
   Src cur;
-  if constexpr (NP > 0) {
-    if (!is_math) {
-      // copy waves: one barrier per step, the same sequence as the math waves
-      if (t0 < t_end) {
-        int e, m0, n0;
-        coords(t0, e, m0, n0);
-        sources(e, m0, n0, cur, false);
+  if (!is_math) {
+    // copy waves: one barrier per step, the same sequence as the math waves
+    if (t0 < t_end) {
+      int e, m0, n0;
+      coords(t0, e, m0, n0);
+      sources(e, m0, n0, cur, false);
 #pragma unroll
-        for (int q = 0; q < STAGES - 1; ++q)
-          if (q < nk) issue(cur, q, q);
-      }
-      // the next tile's sources are computed in step kc; its row ids,
-      // copied to this wave's LDS slot ahead of step STAGES-1's loads, have
-      // landed by then: in-order completion, and the wait of step kt covers
-      // every load issued before step kt+1 (all of them in the last step)
-      const int kc = min(STAGES - 2, nk - 1);
-      for (int t = t0, sb = 0; t < t_end; t += per_xcd, sb = (sb + nk) % STAGES) {
-        const int tn = t + per_xcd;
-        const bool next = tn < t_end;
-        Src nxt;
-        int en = 0, m0n = 0, n0n = 0;
-        if (next) {
-          coords(tn, en, m0n, n0n);
-#pragma unroll
-          for (int q = 0; q < BM / 64; ++q) dma4(g.sorted_ids + m0n + q * 64 + lane, lds_addr(&lds_sid[lw][q * 64]));
-        }
-        // Tiles of at most 32 steps (the second products here) run with
-        // the next tile as one sequence of steps: step j of it is issued in
-        // step j - (STAGES - 1), so the next tile's first steps load STAGES - 1
-        // steps ahead like every other step, and the wait keeps them in
-        // flight across the boundary (fp8 GEMM2 -2.4 %, prefill GEMM2 -2 %).
-        // Longer tiles measured no gain, and tiles of fewer than 2 STAGES
-        // steps may not have the next tile's sources ready in time: both
-        // issue the next tile's first steps together in their last step.
-        const bool flow = next && nk >= 2 * STAGES && nk <= 32;  // uniform
-        for (int kt = 0; kt < nk; ++kt) {
-          wait_ahead(flow ? STAGES - 2 : min(STAGES - 2, nk - 1 - kt));
-          bar();
-          if (next && kt == kc) sources(en, m0n, n0n, nxt, true);
-          const int j = kt + STAGES - 1;
-          if (j < nk) issue(cur, j, (sb + j) % STAGES);
-          else if (flow) issue(nxt, j - nk, (sb + j) % STAGES);
-          if (next && !flow && kt == nk - 1) {
-#pragma unroll
-            for (int q = 0; q < STAGES - 1; ++q)
-              if (q < nk) issue(nxt, q, (sb + nk + q) % STAGES);
-          }
-        }
-        if constexpr (FMT == 1 && GEMM1) {  // the two barriers of the requant epilogue
-          bar();
-          bar();
-        }
-        if (next) cur = nxt;
-      }
-      return;
+      for (int q = 0; q < STAGES - 1; ++q)
+        if (q < nk) issue(cur, q, q);
     }
+    // the next tile's sources are computed in step kc; its row ids,
+    // copied to this wave's LDS slot ahead of step STAGES-1's loads, have
+    // landed by then: in-order completion, and the wait of step kt covers
+    // every load issued before step kt+1 (all of them in the last step)
+    const int kc = min(STAGES - 2, nk - 1);
+    for (int t = t0, sb = 0; t < t_end; t += per_xcd, sb = (sb + nk) % STAGES) {
+      const int tn = t + per_xcd;
+      const bool next = tn < t_end;
+      Src nxt;
+      int en = 0, m0n = 0, n0n = 0;
+      if (next) {
+        coords(tn, en, m0n, n0n);
+#pragma unroll
+        for (int q = 0; q < BM / 64; ++q) dma4(g.sorted_ids + m0n + q * 64 + lane, lds_addr(&lds_sid[lw][q * 64]));
+      }
+      // Tiles of at most 32 steps (the second products here) run with
+      // the next tile as one sequence of steps: step j of it is issued in
+      // step j - (STAGES - 1), so the next tile's first steps load STAGES - 1
+      // steps ahead like every other step, and the wait keeps them in
+      // flight across the boundary (fp8 GEMM2 -2.4 %, prefill GEMM2 -2 %).
+      // Longer tiles measured no gain, and tiles of fewer than 2 STAGES
+      // steps may not have the next tile's sources ready in time: both
+      // issue the next tile's first steps together in their last step.
+      const bool flow = next && nk >= 2 * STAGES && nk <= 32;  // uniform
+      for (int kt = 0; kt < nk; ++kt) {
+        wait_ahead(flow ? STAGES - 2 : min(STAGES - 2, nk - 1 - kt));
+        bar();
+        if (next && kt == kc) sources(en, m0n, n0n, nxt, true);
+        const int j = kt + STAGES - 1;
+        if (j < nk) issue(cur, j, (sb + j) % STAGES);
+        else if (flow) issue(nxt, j - nk, (sb + j) % STAGES);
+        if (next && !flow && kt == nk - 1) {
+#pragma unroll
+          for (int q = 0; q < STAGES - 1; ++q)
+            if (q < nk) issue(nxt, q, (sb + nk + q) % STAGES);
+        }
+      }
+      if constexpr (FMT == 1 && GEMM1) {  // the two barriers of the requant epilogue
+        bar();
+        bar();
+      }
+      if (next) cur = nxt;
+    }
+    return;
   }
 
   for (int t = t0, sb = 0; t < t_end; t += per_xcd, sb = (sb + nk) % STAGES) {
     int e, m0, n0;
     coords(t, e, m0, n0);
-    if constexpr (NP == 0) {
-      __syncthreads();  // the previous tile's buffers are no longer read
-      sources(e, m0, n0, cur, false);
-#pragma unroll
-      for (int q = 0; q < STAGES - 1; ++q)
-        if (q < nk) issue(cur, q, (sb + q) % STAGES);
-    }
-
     // GEMM2: the ids of this lane's output rows, for the epilogue's pad-row
     // check, requested before the K loop (the math waves issue no other
     // global loads, so this one has landed long before it is used)
@@ -533,7 +507,7 @@ void moe_gemm_tiled(GroupedGemm g) {
       live_row = g.sorted_ids[m0 + lane] < g.n_routed;
     } else if constexpr (!GEMM1) {
 #pragma unroll
-      for (int i = 0; i < TM; ++i) sid_ep[i] = g.sorted_ids[m0 + wm * WTM + i * 32 + l32];
+      for (int i = 0; i < TM; ++i) sid_ep[i] = g.sorted_ids[m0 + i * 32 + l32];
     }
     f32x16 acc[TM][TN];
 #pragma unroll
@@ -557,8 +531,8 @@ void moe_gemm_tiled(GroupedGemm g) {
     // top 8, 8192 tokens 6392 and 6180 us; fp8, the same layer, 8192 tokens 4169
     // and 4106 us, 2000 tokens 1894 and 1819, 300 tokens 1235 and 1161.
     constexpr bool I4P = FMT == 2 && KB == 512;  // int4 on the software-pipelined loop
-    constexpr bool SKIP = NP > 0 && (FMT == 0 || FMT == 1 || FMT == 4 || MX8 || I4P);
-    static_assert(!SKIP || (WM == 1 && (TM == 4 || TM == 2)), "every wave holds all row blocks");
+    constexpr bool SKIP = FMT != 2 || I4P;
+    static_assert(TM == 4 || TM == 2, "every wave holds all row blocks");
     int nb = TM;
     if constexpr (SKIP) nb = __popcll(__ballot(lane < TM && g.sorted_ids[m0 + 32 * (lane % TM)] < g.n_routed));
     auto for_blocks = [&](auto loop) {
@@ -567,7 +541,7 @@ void moe_gemm_tiled(GroupedGemm g) {
       else if (nb == 2) loop(std::integral_constant<int, 2>{});
       else loop(std::integral_constant<int, 1>{});
     };
-    if constexpr (NP > 0 && FMT == 0) {
+    if constexpr (FMT == 0) {
       // Math waves of a split bf16 launch: fragments are read one MFMA K
       // substep ahead into a double buffer.  The barrier for stage kt+1 sits
       // before the last substep's MFMAs of step kt (once this wave's reads of
@@ -584,7 +558,7 @@ void moe_gemm_tiled(GroupedGemm g) {
           const int ch = 2 * kk + kg;
 #pragma unroll
           for (int i = 0; i < NB; ++i) {
-            const int r = wm * WTM + i * 32 + l32;
+            const int r = i * 32 + l32;
             fa[buf][i] = as_bf16x8(ld16(As + r * KB + ((ch ^ swz<KB>(r)) << 4)));
           }
 #pragma unroll
@@ -618,7 +592,7 @@ void moe_gemm_tiled(GroupedGemm g) {
         }
       });
     }
-    if constexpr (NP > 0 && FMT == 1) {
+    if constexpr (FMT == 1) {
       // fp8 math waves of a split launch (two waves per SIMD, so at most 256
       // registers each): transposed product as below, but one 32x32 block
       // at a time -- its two K halves are MFMAs on one partial, and the
@@ -646,7 +620,7 @@ void moe_gemm_tiled(GroupedGemm g) {
           }
           i32x8 af[2][2];  // [buffer][K half] of one row block
           auto read_a = [&](int i, int buf) {
-            const int r = wm * WTM + i * 32 + l32;
+            const int r = i * 32 + l32;
 #pragma unroll
             for (int kk = 0; kk < 2; ++kk) af[buf][kk] = read8(As + r * KB, r, kk);
           };
@@ -655,7 +629,7 @@ void moe_gemm_tiled(GroupedGemm g) {
           const float* sB = reinterpret_cast<const float*>(Ss + (BM / 64) * 256);  // [64]
           float fa[NB], sw[TN];
 #pragma unroll
-          for (int i = 0; i < NB; ++i) fa[i] = sA[wm * WTM + i * 32 + l32];
+          for (int i = 0; i < NB; ++i) fa[i] = sA[i * 32 + l32];
 #pragma unroll
           for (int j = 0; j < TN; ++j) {
             const int r = brow(j);
@@ -695,7 +669,7 @@ void moe_gemm_tiled(GroupedGemm g) {
         }
       });
     }
-    if constexpr (NP > 0 && FMT == 4) {
+    if constexpr (FMT == 4) {
       // Math waves of a split MXFP4 launch.  One math wave per SIMD issues in
       // order, so decoding a substep's weights and then multiplying them ran
       // the VALU (its conversions) and the matrix pipe one after the
@@ -720,7 +694,7 @@ void moe_gemm_tiled(GroupedGemm g) {
           const int ch = NKK * kg + kk;
 #pragma unroll
           for (int i = 0; i < NB; ++i) {
-            const int r = wm * WTM + i * 32 + l32;
+            const int r = i * 32 + l32;
             fa[buf][i] = as_bf16x8(ld16(As + r * KB + ((ch ^ swz<KB>(r)) << 4)));
           }
         };
@@ -805,7 +779,7 @@ void moe_gemm_tiled(GroupedGemm g) {
         step(nk - 1, std::true_type{});
       });
     }
-    if constexpr (NP > 0 && MX8) {
+    if constexpr (MX8) {
       // Math waves of an MXFP4 x MXFP8 launch, formed transposed like fp8
       // (the weight fragment is the first operand).  MFMA kk of the step
       // covers K [64 kk, 64 kk + 64) in two 32-element scale blocks, and lane
@@ -1020,114 +994,10 @@ void moe_gemm_tiled(GroupedGemm g) {
         step(nk - 1, std::true_type{});
       });
     }
-    for (int kt = 0; kt < nk && !SKIP; ++kt) {
-      if constexpr (NP == 0) wait_ahead(min(STAGES - 2, nk - 1 - kt));
-      bar();  // every stage-kt copy of every copy wave has landed
-      const bool pre = NP == 0 && kt + STAGES - 1 < nk;  // this wave starts a later stage
-      if (FMT != 0 && pre) issue(cur, kt + STAGES - 1, (sb + kt + STAGES - 1) % STAGES);
-      const uint8_t* As = &smem[(sb + kt) % STAGES][0];
-      const uint8_t* Bs = As + A_BYTES;
-      const uint8_t* Ss = Bs + B_BYTES;
-      if constexpr (FMT == 0) {
-        // every fragment of the K step is requested before the first MFMA
-        constexpr int NKK = KE / 16;  // MFMA K substeps per step
-        bf16x8 af[NKK][TM], bfr[NKK][TN];
-#pragma unroll
-        for (int kk = 0; kk < NKK; ++kk) {
-          const int ch = 2 * kk + kg;
-#pragma unroll
-          for (int i = 0; i < TM; ++i) {
-            const int r = wm * WTM + i * 32 + l32;
-            af[kk][i] = as_bf16x8(ld16(As + r * KB + ((ch ^ swz<KB>(r)) << 4)));
-          }
-#pragma unroll
-          for (int j = 0; j < TN; ++j) {
-            const int r = brow(j) + l32;
-            bfr[kk][j] = as_bf16x8(ld16(Bs + r * BB + ((ch ^ swz<KB>(r)) << 4)));
-          }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        // the next stage's loads are issued between the MFMA groups, so the
-        // matrix pipe keeps running while the address unit takes them
-        constexpr int PER = (A_CH + B_CH + NKK - 1) / NKK;
-#pragma unroll
-        for (int kk = 0; kk < NKK; ++kk) {
-#pragma unroll
-          for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-              acc[i][j] = TRB ? mfma32x32x16(bfr[kk][j], af[kk][i], acc[i][j]) : mfma32x32x16(af[kk][i], bfr[kk][j], acc[i][j]);
-          __builtin_amdgcn_sched_barrier(0);
-          if (pre) issue_part(cur, kt + STAGES - 1, (sb + kt + STAGES - 1) % STAGES, kk * PER, min((kk + 1) * PER, A_CH + B_CH));
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      } else if constexpr (FMT == 1) {
-        // Transposed product: the MFMA's first operand is a 32-row block of
-        // W (output columns n), the second a 32-row block of A (rows m), so
-        // a lane's 16 values run down n for one row m.  Every value of a
-        // lane then shares one A row scale and one W block scale: the K-block
-        // rescale is one multiply per 32x32 block and one fma per value.
-        i32x8 af[2][TM], bfr[2][TN];
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk) {
-          const int c0 = 4 * kk + 2 * kg;
-#pragma unroll
-          for (int i = 0; i < TM; ++i) {
-            const int r = wm * WTM + i * 32 + l32;
-            const i32x4 lo = __builtin_bit_cast(i32x4, ld16(As + r * KB + ((c0 ^ swz<KB>(r)) << 4)));
-            const i32x4 hi = __builtin_bit_cast(i32x4, ld16(As + r * KB + (((c0 + 1) ^ swz<KB>(r)) << 4)));
-            af[kk][i] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-          }
-#pragma unroll
-          for (int j = 0; j < TN; ++j) {
-            const int r = brow(j) + l32;
-            const i32x4 lo = __builtin_bit_cast(i32x4, ld16(Bs + r * BB + ((c0 ^ swz<KB>(r)) << 4)));
-            const i32x4 hi = __builtin_bit_cast(i32x4, ld16(Bs + r * BB + (((c0 + 1) ^ swz<KB>(r)) << 4)));
-            bfr[kk][j] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-          }
-        }
-        const float* sA = reinterpret_cast<const float*>(Ss);                    // [BM]
-        const float* sB = reinterpret_cast<const float*>(Ss + (BM / 64) * 256);  // [64]
-        float fa[TM], sb[TN];
-#pragma unroll
-        for (int i = 0; i < TM; ++i) fa[i] = sA[wm * WTM + i * 32 + l32];
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const int r = brow(j);
-          sb[j] = GEMM1 ? sB[r < NC ? 0 : 1] : sB[(r / 128) % (BNW / 128)];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        // Blocks in pairs: the two K halves of pair q go to the matrix pipe
-        // (independent MFMAs back to back), then the VALU folds pair q-1 into
-        // the accumulators while those run.  Four partial blocks are live.
-        constexpr int NB = TM * TN;
-        static_assert(NB % 2 == 0, "block pairs");
-        f32x16 part[4];
-#pragma unroll
-        for (int q = 0; q <= NB / 2; ++q) {
-          if (q < NB / 2) {
-#pragma unroll
-            for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-              for (int u = 0; u < 2; ++u) {
-                const int bi = 2 * q + u, i = bi / TN, j = bi % TN;
-                f32x16& pp = part[(q & 1) * 2 + u];
-                pp = mfma32x32x64_fp8(bfr[kk][j], af[kk][i], kk == 0 ? f32x16{} : pp);
-              }
-          }
-          if (q > 0) {
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-              const int bi = 2 * (q - 1) + u, i = bi / TN, j = bi % TN;
-              const f32x16& pp = part[((q - 1) & 1) * 2 + u];
-              const float f = fa[i] * sb[j];
-#pragma unroll
-              for (int v = 0; v < 16; ++v) acc[i][j][v] = fmaf(pp[v], f, acc[i][j][v]);
-            }
-          }
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      } else if constexpr (GSUM) {
+    if constexpr (FMT == 2 && !I4P) {
+      for (int kt = 0; kt < nk; ++kt) {
+        bar();  // every stage-kt copy of every copy wave has landed
+        const uint8_t* Ss = &smem[(sb + kt) % STAGES][A_BYTES + B_BYTES];
         // int4.  The codes enter the MFMA exactly, as bf16 136 + q, and
         // the group scale is applied in fp32: acc holds the tile's sum
         // divided by its column's current scale s, so each step first takes
@@ -1157,7 +1027,7 @@ void moe_gemm_tiled(GroupedGemm g) {
         }
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
-          const int r0 = wm * WTM + i * 32 + 4 * kg;  // value v: row r0 + 8*(v/4) + v%4
+          const int r0 = i * 32 + 4 * kg;  // value v: row r0 + 8*(v/4) + v%4
           f32x16 rs{};
 #pragma unroll
           for (int b4 = 0; b4 < (SUMS ? 4 : 0); ++b4) {
@@ -1176,7 +1046,7 @@ void moe_gemm_tiled(GroupedGemm g) {
         // the stage's (rows aligned to their bytes), and the scheduler keeps to
         // one substep at a time: both hold the kernel in 128 registers.
         static_assert(STAGE % 256 == 0 && A_BYTES % 256 == 0, "rows aligned to their size");
-        const int ra = wm * WTM + l32, rb = brow(0) + l32;
+        const int ra = l32, rb = brow(0) + l32;
         const uint32_t st = smem0 + ((sb + kt) % STAGES) * STAGE;
         const uint32_t pa = st + ra * KB + (((NKK * kg) ^ swz<KB>(ra)) << 4);
         const uint32_t pb = st + A_BYTES + rb * BB + (((NBW * kg) ^ swz_b<BB>(rb)) << 4);
@@ -1218,7 +1088,7 @@ void moe_gemm_tiled(GroupedGemm g) {
     // ---- epilogue.  D element v of a 32x32 tile (bf16 / 4-bit GEMM1): row
     // 8*(v/4) + 4*kg + v%4, column l32.  fp8 and every GEMM2 form the product
     // transposed (W is the MFMA's first operand): lane (kg, l32) of row
-    // block i holds row wm*WTM + i*32 + l32 at columns 8*(v/4) + 4*kg + v%4
+    // block i holds row i*32 + l32 at columns 8*(v/4) + 4*kg + v%4
     // of each column block, so four consecutive columns per store.
     if constexpr (GSUM) {
 #pragma unroll
@@ -1239,7 +1109,7 @@ void moe_gemm_tiled(GroupedGemm g) {
           for (int v = 0; v < 16; ++v) av[i][j][v] = silu_mul(acc[i][j][v], acc[i][j + TH][v]);
       if constexpr (FMT == 1) {
         // transposed layout: lane (kg, l32) of row block i holds row
-        // wm*WTM + i*32 + l32 at columns 8*(v/4) + 4*kg + v%4 of each gate
+        // i*32 + l32 at columns 8*(v/4) + 4*kg + v%4 of each gate
         // block.  Row amax over the tile's 128 columns: the lane's values,
         // the other k-group lane, then the WN waves (LDS).
 #pragma unroll
@@ -1251,14 +1121,14 @@ void moe_gemm_tiled(GroupedGemm g) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) m = fmaxf(m, fabsf(av[i][j][v]));
           m = fmaxf(m, __shfl_xor(m, 32));
-          if (kg == 0) lds_amax[wn][wm * WTM + i * 32 + l32] = m;
+          if (kg == 0) lds_amax[wn][i * 32 + l32] = m;
         }
         __syncthreads();
         uint8_t* q = static_cast<uint8_t*>(g.inter);
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
           if (i >= nb) break;
-          const int rl = wm * WTM + i * 32 + l32;
+          const int rl = i * 32 + l32;
           float m = 0.f;
 #pragma unroll
           for (int w = 0; w < WN; ++w) m = fmaxf(m, lds_amax[w][rl]);
@@ -1295,7 +1165,7 @@ void moe_gemm_tiled(GroupedGemm g) {
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
           if (i >= nb) break;  // blocks of pads are never read
-          const size_t row = static_cast<size_t>(m0 + wm * WTM + i * 32 + l32);
+          const size_t row = static_cast<size_t>(m0 + i * 32 + l32);
 #pragma unroll
           for (int j = 0; j < TH; ++j) {
             float m = 0.f;
@@ -1325,7 +1195,7 @@ void moe_gemm_tiled(GroupedGemm g) {
             for (int j = 0; j < TH; ++j)
 #pragma unroll
               for (int v = 0; v < 16; ++v) {
-                const int row = m0 + wm * WTM + i * 32 + 8 * (v >> 2) + 4 * kg + (v & 3);
+                const int row = m0 + i * 32 + 8 * (v >> 2) + 4 * kg + (v & 3);
                 // int4: eight columns in the order the second product's codes decode to
                 const int lc = FMT == 2 ? (l32 & ~7) | (l32 & 3) << 1 | (l32 >> 2 & 1) : l32;
                 const int col = n0 + wn * (WTN / 2) + j * 32 + lc;
@@ -1344,7 +1214,7 @@ void moe_gemm_tiled(GroupedGemm g) {
       // 1608 -> 1502 us)
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
-        const int row = m0 + wm * WTM + i * 32 + l32;
+        const int row = m0 + i * 32 + l32;
         if (sid_ep[i] >= g.n_routed) continue;  // pad rows are never read
         uint16_t* yr = static_cast<uint16_t*>(g.y) + static_cast<size_t>(row) * g.H;
 #pragma unroll
@@ -1374,7 +1244,7 @@ void moe_gemm_tiled(GroupedGemm g) {
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          const int r = wm * WTM + i * 32 + 8 * (v >> 2) + (v & 3);
+          const int r = i * 32 + 8 * (v >> 2) + (v & 3);
           if (r >= live) continue;  // pad rows are never read
           float* yr = static_cast<float*>(g.y) + static_cast<size_t>(m0 + r + 4 * kg) * g.H + n0 + wn * WTN + l32;
 #pragma unroll
@@ -1396,7 +1266,7 @@ void moe_gemm_tiled(GroupedGemm g) {
       const bool wide = least < 0x1p-64f;
       if (__builtin_expect(wide || !(top < INFINITY), 0)) {
         for (int b = 0; b < TM * 16 * TN; ++b) {
-          const int r = wm * WTM + (b / TN / 16) * 32 + 8 * (b / TN % 16 >> 2) + (b / TN & 3);
+          const int r = (b / TN / 16) * 32 + 8 * (b / TN % 16 >> 2) + (b / TN & 3);
           if (r >= live) continue;
           const size_t row = static_cast<size_t>(m0 + r + 4 * kg);
           const int n = n0 + wn * WTN + b % TN * 32 + l32;
@@ -1413,7 +1283,7 @@ void moe_gemm_tiled(GroupedGemm g) {
       const bool masked = n0 + NC > g.H;  // uniform: only a ragged last column tile masks
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
-        const int row = m0 + wm * WTM + i * 32 + l32;
+        const int row = m0 + i * 32 + l32;
         if (sid_ep[i] >= g.n_routed) continue;  // pad rows are never read
         float* yr = static_cast<float*>(g.y) + static_cast<size_t>(row) * g.H;
 #pragma unroll
@@ -1458,17 +1328,16 @@ dim3 persistent_grid(int per_cu, long max_tiles) {
   return dim3(static_cast<unsigned>(std::max<long>(kXcds, std::min(n, cap))));
 }
 
-template <int FMT, bool GEMM1, int BM, int BNW, int WM, int WN, int GM, int KBT = 128, int STAGES = 3, int NP = 0,
-          int OPT = 0>
+template <int FMT, bool GEMM1, int BM, int BNW, int GM, int KBT, int STAGES, int OPT = 0>
 hipError_t launch_tiled(const GroupedGemm& g, hipStream_t s) {
   constexpr int NC = GEMM1 ? BNW / 2 : BNW;
-  constexpr int NT = (WM * WN + NP) * 64;
+  constexpr int NT = (kMathWaves + kCopyWaves) * 64;
   // only bf16 handles a ragged last K step; every other format's steps must
   // tile K exactly (a step past K would read beyond its rows)
   constexpr int KE = (FMT == 1 || FMT == 5) ? KBT : KBT / 2;
   if (FMT != 0 && (GEMM1 ? g.H : g.I) % KE != 0) return hipErrorInvalidValue;
   const long mt = g.max_rows / BM, nt = ((GEMM1 ? g.I : g.H) + NC - 1) / NC;
-  auto kern = moe_gemm_tiled<FMT, GEMM1, BM, BNW, WM, WN, GM, KBT, STAGES, NP, OPT>;
+  auto kern = moe_gemm_tiled<FMT, GEMM1, BM, BNW, GM, KBT, STAGES, OPT>;
   // workgroups per CU depend on the kernel's registers and LDS only: queried
   // once per instantiation (thread-safe static initialisation)
   static const int per_cu = occupancy_per_cu(kern, NT);
@@ -1478,118 +1347,51 @@ hipError_t launch_tiled(const GroupedGemm& g, hipStream_t s) {
 
 }  // namespace
 
-// Whether the weights of experts with one row tile are copied with the
-// non-temporal hint, for bf16 and fp8: where experts have at most a tile of rows on
-// average.  Layers without and with it, the same weights as in the call before and,
-// second, after 1 GB of other reads: bf16, 4096 x 1408 x 64 experts, top 6, 777
-// tokens (73 rows per expert) 495 -> 473 us, -4.3 %; 1200 (112) -1.2 %, -0.8 %; 2500 (234)
-// +0.2 %, +0.8 %; 4096 (384) +0.7 %, +0.8 %, the choice alone; fp8, 7168 x 2048 x 256
-// experts, top 8, 300 tokens (9) 1245 -> 1162, -6.2 %; 4000 (125) -0.7 %, -1.0 %.  The
-// 256-element int4 steps always take it, for little: 4096 x 1536 x 128 experts, top 8,
-// 512 tokens -1.5 %, +0.4 %, 2048 -0.7 %, -1.7 %, 5120 x 1536 x 160, top 6, 200 tokens +0.9 %,
-// +2.0 %.  MXFP4 x MXFP8 has no use for it: 2048 x 1408 x 60 experts, top 4, 260
+// Whether the bf16 kernels copy the weights of experts with one row tile with the
+// non-temporal hint: where experts have at most a tile of rows on average.  Layers
+// without and with it, the same weights as in the call before and, second, after
+// 1 GB of other reads: 4096 x 1408 x 64 experts, top 6, 777 tokens (73 rows per
+// expert) 495 -> 473 us, -4.3 %; 1200 (112) -1.2 %, -0.8 %; 2500 (234) +0.2 %, +0.8 %; 4096
+// (384) +0.7 %, +0.8 %, the choice alone.  The fp8 kernels always do: 7168 x 2048 x 256
+// experts, top 8, 300 tokens (9) 1245 -> 1162, -6.2 %; 4000 (125) -0.7 %, -1.0 %; 8192 (256)
+// -1.0 %, -1.0 %.  So do the 256-element int4 steps, for little: 4096 x 1536 x 128 experts,
+// top 8, 512 tokens -1.5 %, +0.4 %, 2048 -0.7 %, -1.7 %, 5120 x 1536 x 160, top 6, 200 tokens
+// +0.9 %, +2.0 %.  MXFP4 x MXFP8 has no use for it: 2048 x 1408 x 60 experts, top 4, 260
 // tokens +14 %, +2.5 % (weights that the memory-side cache held from call to call no
 // longer stay there), 7168 x 2048 x 256, 1000 tokens -0.1 %, +0.1 %.  Nor has MXFP4, as far
 // as measured (8192 tokens 6243 -> 6332 us).
 bool weights_once(const GroupedGemm& g) { return g.n_routed <= 128L * g.E; }
 
-// bf16 tile shapes: rows x weight rows per workgroup, waves as WM x WN.
-#ifndef MOE_T1_BNW
-#define MOE_T1_BNW 256
-#define MOE_T1_WM 1
-#define MOE_T1_WN 4
-#endif
-#ifndef MOE_T2_BNW
-#define MOE_T2_BNW 256
-#define MOE_T2_WM 1
-#define MOE_T2_WN 4
-#endif
-#ifndef MOE_TBF_BM
-#define MOE_TBF_BM 128
-#endif
-#ifndef MOE_TBF_KB
-#define MOE_TBF_KB 128
-#endif
-#ifndef MOE_TBF_STAGES
-#define MOE_TBF_STAGES 3
-#endif
-// Copy waves beside the math waves (0: the math waves copy).  Every tiled
-// launch uses four; the 64-row int4 kernels are held to 128 registers so two
-// workgroups of eight waves still fit per CU.
-#ifndef MOE_TBF_NP1
-#define MOE_TBF_NP1 4
-#endif
-#ifndef MOE_TBF_NP2
-#define MOE_TBF_NP2 4
-#endif
-#ifndef MOE_TI4_NP1
-#define MOE_TI4_NP1 4
-#endif
-#ifndef MOE_TI4_NP2
-#define MOE_TI4_NP2 4
-#endif
 // most row tiles of one expert swept together per column tile
-#ifndef MOE_TGM
-#define MOE_TGM 8
-#endif
-#ifndef MOE_TGM_INT4
-#define MOE_TGM_INT4 16
-#endif
-int bf16_tiled_block_m() { return MOE_TBF_BM; }
-template <bool GEMM1, int BNW, int WM, int WN, int NP>
+constexpr int kSweep = 8, kSweepInt4 = 16;
+
+int bf16_tiled_block_m() { return 128; }
+template <bool GEMM1, int BNW>
 hipError_t launch_bf16(const GroupedGemm& g, hipStream_t s) {
-  if (weights_once(g)) return launch_tiled<0, GEMM1, MOE_TBF_BM, BNW, WM, WN, MOE_TGM, MOE_TBF_KB, MOE_TBF_STAGES, NP, kOnce>(g, s);
-  return launch_tiled<0, GEMM1, MOE_TBF_BM, BNW, WM, WN, MOE_TGM, MOE_TBF_KB, MOE_TBF_STAGES, NP>(g, s);
+  if (weights_once(g)) return launch_tiled<0, GEMM1, 128, BNW, kSweep, 128, 3, kOnce>(g, s);
+  return launch_tiled<0, GEMM1, 128, BNW, kSweep, 128, 3>(g, s);
 }
-hipError_t launch_gemm1_bf16_tiled(const GroupedGemm& g, hipStream_t s) {
-  return launch_bf16<true, MOE_T1_BNW, MOE_T1_WM, MOE_T1_WN, MOE_TBF_NP1>(g, s);
-}
+hipError_t launch_gemm1_bf16_tiled(const GroupedGemm& g, hipStream_t s) { return launch_bf16<true, 256>(g, s); }
 hipError_t launch_gemm2_bf16_tiled(const GroupedGemm& g, hipStream_t s) {
-  if (g.H % MOE_T2_BNW) return launch_bf16<false, 128, MOE_T2_WM, MOE_T2_WN, MOE_TBF_NP2>(g, s);
-  return launch_bf16<false, MOE_T2_BNW, MOE_T2_WM, MOE_T2_WN, MOE_TBF_NP2>(g, s);
+  if (g.H % 256) return launch_bf16<false, 128>(g, s);
+  return launch_bf16<false, 256>(g, s);
 }
 
-// fp8 over the 128 x 256 tile: with copy waves (NP > 0) four math waves
-// (1 x 4), else eight (MOE_F8_WM x MOE_F8_WN) that copy for themselves
-#ifndef MOE_F8_WM
-#define MOE_F8_WM 2
-#define MOE_F8_WN 4
-#endif
-#ifndef MOE_F8_NP1
-#define MOE_F8_NP1 4
-#endif
-#ifndef MOE_F8_NP2
-#define MOE_F8_NP2 4
-#endif
 int gemm_block_m_fp8(int, int, int) { return 128; }
-template <bool GEMM1, int BNW, int NP>
+template <bool GEMM1, int BNW>
 hipError_t launch_fp8(const GroupedGemm& g, hipStream_t s) {
-  if constexpr (NP > 0) {
-    if (weights_once(g)) return launch_tiled<1, GEMM1, 128, BNW, 1, 4, MOE_TGM, 128, 3, NP, kOnce>(g, s);
-    return launch_tiled<1, GEMM1, 128, BNW, 1, 4, MOE_TGM, 128, 3, NP>(g, s);
-  } else return launch_tiled<1, GEMM1, 128, BNW, MOE_F8_WM, MOE_F8_WN, MOE_TGM>(g, s);
+  return launch_tiled<1, GEMM1, 128, BNW, kSweep, 128, 3, kOnce>(g, s);
 }
-hipError_t launch_gemm1_fp8(const GroupedGemm& g, hipStream_t s) {
-  return launch_fp8<true, 256, MOE_F8_NP1>(g, s);
-}
+hipError_t launch_gemm1_fp8(const GroupedGemm& g, hipStream_t s) { return launch_fp8<true, 256>(g, s); }
 hipError_t launch_gemm2_fp8(const GroupedGemm& g, hipStream_t s) {
-  if (g.H % 256) return launch_fp8<false, 128, MOE_F8_NP2>(g, s);
-  return launch_fp8<false, 256, MOE_F8_NP2>(g, s);
+  if (g.H % 256) return launch_fp8<false, 128>(g, s);
+  return launch_fp8<false, 256>(g, s);
 }
 
-// int4 row tile: one math wave per 64 columns covers all MOE_TI4_BM rows, so
-// each decoded weight fragment feeds MOE_TI4_BM / 32 MFMAs
-#ifndef MOE_TI4_BM
-#define MOE_TI4_BM 64
-#endif
-// 128 K elements per step: 64 bytes of each int4 weight row (half a cache
-// line, where 64 elements took a quarter), 256 bytes of each activation row;
-// two stages keep two workgroups per CU
-#ifndef MOE_TI4_KB
-#define MOE_TI4_KB 256
-#define MOE_TI4_STAGES 2
-#endif
-int gemm_block_m_int4(int, int, int) { return MOE_TI4_BM; }
+// int4 row tile: one math wave per 64 columns covers all 64 rows, so each decoded
+// weight fragment feeds two MFMAs
+constexpr int kInt4BM = 64;
+int gemm_block_m_int4(int, int, int) { return kInt4BM; }
 // Where GEMM2 finds the intermediate's group sums: each of its tiles, BNW
 // columns wide, reads them from its own part of y (64 rows, room for BNW groups
 // of 64 sums), which it overwrites when it has read them all.  An intermediate of
@@ -1602,7 +1404,7 @@ int int4_sum_columns(int H, int I) {
   return I > 256 && I / 128 <= bnw ? bnw : 0;
 }
 // 256 K elements per step (whole weight lines) leave room for one workgroup per
-// CU, 128 for two, which hide each other's first steps and epilogues.  256 where
+// CU, 128 (64 bytes of each weight row, half a line) for two, which hide each other's first steps and epilogues.  256 where
 // K is a multiple of that and long (1536: 512 tokens, 128 experts 359 us, 388
 // with 128), or each workgroup has one tile at most (H = I = 512, 32 experts, top
 // 4, 150 tokens: 33.8 and 36.8 us).  Short K with many tiles takes 128 (8192
@@ -1611,36 +1413,25 @@ template <bool GEMM1, int BNW>
 bool int4_long_steps(const GroupedGemm& g) {
   const int K = GEMM1 ? g.H : g.I, N = GEMM1 ? g.I : g.H;
   constexpr int NC = GEMM1 ? BNW / 2 : BNW;
-  const long tiles = static_cast<long>(g.max_rows / MOE_TI4_BM) * ((N + NC - 1) / NC);
+  const long tiles = static_cast<long>(g.max_rows / kInt4BM) * ((N + NC - 1) / NC);
   return K % 256 == 0 && (K >= 1536 || tiles <= cu_count());
 }
 template <bool GEMM1, int BNW>
 hipError_t launch_int4(const GroupedGemm& g, hipStream_t s) {
   if constexpr (!GEMM1)
-    if (!g.inter_sums) return launch_tiled<2, false, MOE_TI4_BM, BNW, 1, 4, MOE_TGM_INT4, MOE_TI4_KB, MOE_TI4_STAGES, MOE_TI4_NP2, kNoSums>(g, s);
-  if (int4_long_steps<GEMM1, BNW>(g)) return launch_tiled<2, GEMM1, MOE_TI4_BM, BNW, 1, 4, MOE_TGM_INT4, 512, 2, 4, kOnce>(g, s);
-  return launch_tiled<2, GEMM1, MOE_TI4_BM, BNW, 1, 4, MOE_TGM_INT4, MOE_TI4_KB, MOE_TI4_STAGES, GEMM1 ? MOE_TI4_NP1 : MOE_TI4_NP2>(g, s);
+    if (!g.inter_sums) return launch_tiled<2, false, kInt4BM, BNW, kSweepInt4, 256, 2, kNoSums>(g, s);
+  if (int4_long_steps<GEMM1, BNW>(g)) return launch_tiled<2, GEMM1, kInt4BM, BNW, kSweepInt4, 512, 2, kOnce>(g, s);
+  return launch_tiled<2, GEMM1, kInt4BM, BNW, kSweepInt4, 256, 2>(g, s);
 }
 hipError_t launch_gemm1_int4(const GroupedGemm& g, hipStream_t s) { return launch_int4<true, 256>(g, s); }
 // MXFP4 weights (same 4-bit packing as int4, E8M0 scales per 32)
-#ifndef MOE_TMX_BM
-#define MOE_TMX_BM 128
-#endif
-int gemm_block_m_mxfp4() { return MOE_TMX_BM; }
+int gemm_block_m_mxfp4() { return 128; }
 hipError_t launch_gemm1_mxfp4_tiled(const GroupedGemm& g, hipStream_t s) {
-  if constexpr (MOE_TMX_BM == 64)
-    return launch_tiled<4, true, 64, 256, 1, 4, MOE_TGM_INT4, MOE_TI4_KB, MOE_TI4_STAGES, MOE_TI4_NP1>(g, s);
-  else
-    return launch_tiled<4, true, 128, 256, 1, 4, MOE_TGM, 256, 3, 4>(g, s);
+  return launch_tiled<4, true, 128, 256, kSweep, 256, 3>(g, s);
 }
 hipError_t launch_gemm2_mxfp4_tiled(const GroupedGemm& g, hipStream_t s) {
-  if constexpr (MOE_TMX_BM == 64) {
-    if (g.H % 256) return launch_tiled<4, false, 64, 128, 1, 4, MOE_TGM_INT4, MOE_TI4_KB, MOE_TI4_STAGES, MOE_TI4_NP2>(g, s);
-    return launch_tiled<4, false, 64, 256, 1, 4, MOE_TGM_INT4, MOE_TI4_KB, MOE_TI4_STAGES, MOE_TI4_NP2>(g, s);
-  } else {
-    if (g.H % 256) return launch_tiled<4, false, 128, 128, 1, 4, MOE_TGM, 256, 3, 4>(g, s);
-    return launch_tiled<4, false, 128, 256, 1, 4, MOE_TGM, 256, 3, 4>(g, s);
-  }
+  if (g.H % 256) return launch_tiled<4, false, 128, 128, kSweep, 256, 3>(g, s);
+  return launch_tiled<4, false, 128, 256, kSweep, 256, 3>(g, s);
 }
 // MXFP4 weights x MXFP8 activations: the fp8 tile (128 x 256, four math
 // waves beside four copy waves).  When K is a multiple of 256, 256-element K
@@ -1651,8 +1442,8 @@ hipError_t launch_gemm2_mxfp4_tiled(const GroupedGemm& g, hipStream_t s) {
 template <bool GEMM1, int BNW>
 hipError_t launch_mx8(const GroupedGemm& g, hipStream_t s) {
   const int K = GEMM1 ? g.H : g.I;
-  if (K % 256 == 0) return launch_tiled<5, GEMM1, 128, BNW, 1, 4, MOE_TGM, 256, 2, 4>(g, s);
-  return launch_tiled<5, GEMM1, 128, BNW, 1, 4, MOE_TGM, 128, 4, 4>(g, s);
+  if (K % 256 == 0) return launch_tiled<5, GEMM1, 128, BNW, kSweep, 256, 2>(g, s);
+  return launch_tiled<5, GEMM1, 128, BNW, kSweep, 128, 4>(g, s);
 }
 hipError_t launch_gemm1_mx8(const GroupedGemm& g, hipStream_t s) { return launch_mx8<true, 256>(g, s); }
 hipError_t launch_gemm2_mx8(const GroupedGemm& g, hipStream_t s) {
