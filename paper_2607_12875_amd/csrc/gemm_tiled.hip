@@ -15,10 +15,13 @@
 //  int4  A bf16; B signed int4 words decoded in registers to the exact bf16
 //        136 + q right before the bf16 MFMA, never materialised; the bias comes
 //        off through the activations' group sums and the group scale is applied
-//        to the fp32 sums.  VALU-bound by the decode at two workgroups per CU:
-//        with 7 operations per word (14 in the first product and 28, a rounded
-//        q * scale per code, in the second before) a layer of 512 tokens,
-//        4096 x 1536 x 128 experts, top 8, takes 388 us (433).
+//        to the fp32 sums.  The decode takes 7 operations per word; on long K
+//        it is interleaved with the MFMAs, one workgroup per CU and 256
+//        elements per step, so that each weight row gives whole lines: a layer of
+//        512 tokens, 4096 x 1536 x 128 experts, top 8, takes 365 us (388 with
+//        128-element steps and two workgroups per CU, where the decode sets the
+//        time; 433 with 14 and 28 operations per word).  Short K with many tiles
+//        takes the 128-element steps.
 //  mxfp4 A bf16; B OCP MX E2M1 codes with an E8M0 scale per 32 elements,
 //        decoded by v_cvt_scalef32_pk_bf16_fp4 (exact: the bf16 result is the
 //        code's value times a power of two) right before the bf16 MFMA.
@@ -27,8 +30,9 @@
 // goes out in 16-byte stores).
 //
 // Each K step streams KB bytes of every A row through LDS -- 128 (64 bf16 /
-// 128 fp8 elements), or 256 for the 4-bit formats (128 elements, so each
-// weight row gives 64 bytes, half a cache line) -- in 16-byte chunks XOR-swizzled by row
+// 128 fp8 elements), 256 for the 4-bit weights (128 elements beside bf16
+// activations, where each weight row gives 64 bytes, half a cache line; 256 beside
+// MXFP8, a whole one) or 512 (256 elements, int4) -- in 16-byte chunks XOR-swizzled by row
 // so that the fragment reads are bank-conflict free; B rows likewise.
 //
 // Scheduling is persistent and XCD-aware: the launch has a few workgroups per
@@ -499,8 +503,7 @@ void moe_gemm_tiled(GroupedGemm g) {
     int e, m0, n0;
     coords(t, e, m0, n0);
     // GEMM2: the ids of this lane's output rows, for the epilogue's pad-row
-    // check, requested before the K loop (the math waves issue no other
-    // global loads, so this one has landed long before it is used)
+    // check, requested before the K loop (landed long before it is used)
     int sid_ep[GEMM1 ? 1 : TM];
     bool live_row = false;  // int4: row m0 + lane of the tile
     if constexpr (!GEMM1 && FMT == 2) {
@@ -524,12 +527,15 @@ void moe_gemm_tiled(GroupedGemm g) {
                        : wn * WTN + (j) * 32)
 
     // Row blocks (of 32) of the tile that hold routed rows: the last tile of an
-    // expert is padded, on average by half a tile, and the split loops below
-    // leave the blocks of pads out (every wave holds all BM rows, so all gain alike).  Layer
-    // before and after: bf16, 4096 x 1408 x 64 experts, top 6, 4096 tokens 1198
-    // and 1181 us, 777 tokens 506 and 498; MXFP4, 7168 x 2048 x 256 experts,
-    // top 8, 8192 tokens 6392 and 6180 us; fp8, the same layer, 8192 tokens 4169
-    // and 4106 us, 2000 tokens 1894 and 1819, 300 tokens 1235 and 1161.
+    // expert is padded, on average by half a tile, and the loops below
+    // leave the blocks of pads out (every wave holds all BM rows, so all gain alike).
+    // Layer with all blocks and without those of pads: bf16, 4096 x 1408 x 64
+    // experts, top 6, 777 tokens 490 and 479 us, 2500 tokens 861 and 847, 4096 tokens (384
+    // rows per expert) 1223 and 1233; MXFP4, 7168 x 2048 x 256 experts, top 8, 2000 tokens
+    // 2345 and 2098, 8192 tokens 6377 and 6288; MXFP4 x MXFP8 3634 and 3594; fp8, the
+    // same layer, 300 tokens 1241 and 1159, 8192 tokens 4266 and 4172; int4, 4096 x
+    // 1536 x 128 experts, top 8, 512 tokens 394 and 371.  The ids are
+    // waited for at the start of each tile.
     constexpr bool I4P = FMT == 2 && KB == 512;  // int4 on the software-pipelined loop
     constexpr bool SKIP = FMT != 2 || I4P;
     static_assert(TM == 4 || TM == 2, "every wave holds all row blocks");
@@ -1085,8 +1091,8 @@ void moe_gemm_tiled(GroupedGemm g) {
     }
 #undef brow
 
-    // ---- epilogue.  D element v of a 32x32 tile (bf16 / 4-bit GEMM1): row
-    // 8*(v/4) + 4*kg + v%4, column l32.  fp8 and every GEMM2 form the product
+    // ---- epilogue.  D element v of a 32x32 tile (GEMM1 with bf16 activations, int4
+    // GEMM2): row 8*(v/4) + 4*kg + v%4, column l32.  The others form the product
     // transposed (W is the MFMA's first operand): lane (kg, l32) of row
     // block i holds row i*32 + l32 at columns 8*(v/4) + 4*kg + v%4
     // of each column block, so four consecutive columns per store.
