@@ -215,10 +215,10 @@ hipError_t launch_act_quant_mx(const uint16_t* x, int M, int K, uint8_t* q, uint
 // off their biased codes (136 + q), on the sixteen lanes (one DPP row) that own
 // the group, eight columns v each, as in the quantiser above.
 __device__ __forceinline__ float biased_group_sum(const uint4& v) {
-  const uint16_t* h = reinterpret_cast<const uint16_t*>(&v);
+  const uint32_t w[4] = {v.x, v.y, v.z, v.w};
   float sum = 0.f;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) sum += bf16_to_f32(h[i]);
+  for (int i = 0; i < 4; ++i) sum += __uint_as_float(w[i] << 16) + __uint_as_float(w[i] & 0xFFFF0000u);
   sum += dpp_f32<0xB1>(sum);
   sum += dpp_f32<0x4E>(sum);
   sum += dpp_f32<0x141>(sum);
