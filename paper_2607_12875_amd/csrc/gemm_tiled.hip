@@ -38,8 +38,8 @@
 // Scheduling is persistent and XCD-aware: the launch has a few workgroups per
 // CU; workgroups that land on one XCD (block ids congruent mod 8) own one
 // contiguous range of logical tiles, ordered expert by expert in chunks of at
-// most GM row tiles x all column tiles, so the weight slab and row tiles that
-// concurrently running workgroups share are read from HBM about once.  The
+// most GM row tiles x all column tiles, so that concurrently running workgroups
+// share a weight slab and row tiles in L2 as long as they stay in step.  The
 // number of real row tiles is read on the device from expert_offsets[E]
 // (segments are padded to BM).
 #include <algorithm>
@@ -535,7 +535,10 @@ void moe_gemm_tiled(GroupedGemm g) {
     // 2345 and 2098, 8192 tokens 6377 and 6288; MXFP4 x MXFP8 3634 and 3594; fp8, the
     // same layer, 300 tokens 1241 and 1159, 8192 tokens 4266 and 4172; int4, 4096 x
     // 1536 x 128 experts, top 8, 512 tokens 394 and 371.  The ids are
-    // waited for at the start of each tile.
+    // waited for at the start of each tile.  Tiles that take unequal time let the
+    // workgroups that share operands drift apart: GEMM1 reads 2.26 GB from HBM with all
+    // blocks and 3.93 without for bf16 at 4096 tokens, 6.91 and 16.8 for MXFP4 at 8192,
+    // 9.54 and 10.6 for fp8, which takes back what the MFMAs save in large bf16 batches.
     constexpr bool I4P = FMT == 2 && KB == 512;  // int4 on the software-pipelined loop
     constexpr bool SKIP = FMT != 2 || I4P;
     static_assert(TM == 4 || TM == 2, "every wave holds all row blocks");
